@@ -50,7 +50,7 @@ def listed():
         dict(name="ensemble_32", kind="batch", op="step", nsteps=2, nruns=32, draw=2109),
         # the warped mesh and ideal MHD (weak form; entropy-conservative) at production size
         dict(name="curved_32", kind="curved", op="step", nsteps=2, polydeg=3, k=32),
-        dict(name="alfven_32", kind="mhd", op="step", nsteps=2, polydeg=3, k=32, volume="weak",
+        dict(name="alfven_32", kind="mhd", op="step", nsteps=4, polydeg=3, k=32, volume="weak",
              surface="hll"),
         dict(name="alfven_ec_20", kind="mhd", op="step", nsteps=4, polydeg=3, k=20, volume="ec",
              surface="ec"),
@@ -160,13 +160,18 @@ def prepare(case, seed):
     u = u.contiguous()
     t = torch.full((1,), time, dtype=torch.float64, device="cuda")
     du = torch.empty_like(u) if case["op"] == "rhs" else None
-    return dict(case=case, solver=solver, u=u, t=t, du=du, time=time)
+    u0 = u.clone() if case["kind"] == "mhd" and case["op"] == "step" else None
+    return dict(case=case, solver=solver, u=u, t=t, du=du, time=time, u0=u0)
 
 
 def run(state):
     case, solver, u = state["case"], state["solver"], state["u"]
     if case["op"] == "rhs":
         return solver.rhs(u, state["du"], t=state["time"])
+    if state.get("u0") is not None:
+        # without divergence control the Alfven wave does not stay smooth for thousands of
+        # steps: a pass starts from the stored state, as a convergence study's does
+        u.copy_(state["u0"])
     solver.step(u, case["nsteps"], cfl=CFL, t=state["t"])
     return {"u": u, "t": state["t"]}
 
