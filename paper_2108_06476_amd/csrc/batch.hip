@@ -35,14 +35,18 @@ struct dgx_batch_s {
   std::vector<void*> allocs;
   std::vector<RunDesc> desc;      // host copy
   RunDesc* desc_d = nullptr;
-  int* order_d = nullptr;
-  int* prefix_d = nullptr;
   int* flag_d = nullptr;
-  std::vector<int> order;
+  // Groups of runs that a kernel takes in one launch (device lists order_d and prefix_d): every
+  // run (the wave speeds), the runs in tiles of the current shape, and, of each polydeg, the
+  // runs with a line of nodes per thread.
+  enum { ALL = 0, TILED = 1, PENCIL = 2, GROUPS = PENCIL + BATCH_NMAX - BATCH_NMIN + 1 };
+  int* order_d[GROUPS] = {};
+  int* prefix_d[GROUPS] = {};
+  std::vector<int> order[GROUPS];
+  BatchLaunch bl[GROUPS] = {};
   int budget = 256;
-  int grid = 0;
+  int grid = 0;       // blocks of the TILED launch
   int cus = 0;
-  BatchLaunch bl{};
   hipStream_t cap = nullptr;
   hipGraph_t graph = nullptr;
   hipGraphExec_t gexec = nullptr;
@@ -99,21 +103,54 @@ void drop_graph(dgx_batch b) {
   b->graph_cfl = -1.0;
 }
 
-// work items of the current block size: runs heaviest (highest polydeg) first
-dgx_status set_shape(dgx_batch b, int budget, int grid) {
-  std::vector<int> prefix(b->nruns + 1, 0);
-  for (int i = 0; i < b->nruns; ++i) {
-    const int r = b->order[i];
-    const int ne = batch_tile_elems(b->desc[r].N, budget);
+// The device lists of a group: its runs' tile counts for `elems(N)` elements per tile.
+template <typename Elems>
+dgx_status upload_group(dgx_batch b, int gi, Elems elems) {
+  const std::vector<int>& order = b->order[gi];
+  const int nr = (int)order.size();
+  std::vector<int> prefix(nr + 1, 0);
+  for (int i = 0; i < nr; ++i) {
+    const int r = order[i], ne = elems(b->desc[r].N);
     prefix[i + 1] = prefix[i] + (b->desc[r].E + ne - 1) / ne;
   }
+  if (nr > 0)
+    BHIP(b, hipMemcpy(b->order_d[gi], order.data(), sizeof(int) * nr, hipMemcpyHostToDevice));
+  BHIP(b, hipMemcpy(b->prefix_d[gi], prefix.data(), sizeof(int) * (nr + 1), hipMemcpyHostToDevice));
+  b->bl[gi].runs = b->desc_d;
+  b->bl[gi].order = b->order_d[gi];
+  b->bl[gi].prefix = b->prefix_d[gi];
+  b->bl[gi].nruns = nr;
+  b->bl[gi].total = prefix[nr];
+  return DGX_OK;
+}
+
+int round8(int n) { return ((n + 7) / 8) * 8; }   // blocks: a multiple of the 8 XCDs
+
+// work items of the current block size: runs heaviest (highest polydeg) first
+dgx_status set_shape(dgx_batch b, int budget, int grid) {
   BHIP(b, hipStreamSynchronize(b->stream));
-  BHIP(b, hipMemcpy(b->prefix_d, prefix.data(), sizeof(int) * (b->nruns + 1), hipMemcpyHostToDevice));
+  for (int gi : {(int)dgx_batch_s::ALL, (int)dgx_batch_s::TILED}) {
+    dgx_status st = upload_group(b, gi, [&](int N) { return batch_tile_elems(N, budget); });
+    if (st != DGX_OK) return st;
+  }
   b->budget = budget;
-  b->bl.total = prefix[b->nruns];
-  // grid 0 or >= the items: one block per item (rounded to the 8 XCDs)
-  b->grid = (grid <= 0 || grid >= b->bl.total) ? ((b->bl.total + 7) / 8) * 8 : grid;
+  // grid 0 or >= the items: one block per item
+  const int total = b->bl[dgx_batch_s::TILED].total;
+  b->grid = (grid <= 0 || grid >= total) ? round8(total) : grid;
   drop_graph(b);
+  return DGX_OK;
+}
+
+// One RK stage (or right-hand side) of every run.
+dgx_status enqueue_stage(dgx_batch b, hipStream_t st, int epi, int cur, double A, double B,
+                         int emit, int kw) {
+  if (b->bl[dgx_batch_s::TILED].total > 0)
+    BHIP(b, batch_stage(st, b->bl[dgx_batch_s::TILED], b->budget, b->grid, b->prec, epi, cur, A, B,
+                        emit, kw));
+  for (int N = BATCH_NMAX; N >= BATCH_NMIN; --N) {
+    const BatchLaunch& l = b->bl[dgx_batch_s::PENCIL + N - BATCH_NMIN];
+    if (l.total > 0) BHIP(b, batch_pencil_stage(st, l, N, epi, cur, A, B, emit, kw));
+  }
   return DGX_OK;
 }
 
@@ -147,12 +184,11 @@ dgx_status bind(dgx_batch b, double* const* u, double* const* du, double* t) {
   return DGX_OK;
 }
 
-dgx_status enqueue_step(dgx_batch b, hipStream_t st, double cfl, bool emit) {
+dgx_status enqueue_step(dgx_batch b, hipStream_t st, double cfl, int cur, bool emit) {
   BHIP(b, batch_dt(st, b->desc_d, b->nruns, cfl));
-  int cur = 0;
   for (int s = 0; s < 5; ++s) {
-    BHIP(b, batch_stage(st, b->bl, b->budget, b->grid, b->prec, EPI_RK, cur, CK_A[s], CK_B[s],
-                        (emit && s == 4) ? 1 : 0, s < 4));
+    dgx_status r = enqueue_stage(b, st, EPI_RK, cur, CK_A[s], CK_B[s], (emit && s == 4) ? 1 : 0, s < 4);
+    if (r != DGX_OK) return r;
     cur = 1 - cur;
   }
   return DGX_OK;
@@ -161,15 +197,8 @@ dgx_status enqueue_step(dgx_batch b, hipStream_t st, double cfl, bool emit) {
 // Two steps: the state returns to the caller's buffer (10 stages).  The second step's
 // last stage emits the wave speeds of the next step, so the graph can be replayed.
 dgx_status enqueue_two_steps(dgx_batch b, hipStream_t st, double cfl) {
-  BHIP(b, batch_dt(st, b->desc_d, b->nruns, cfl));
-  int cur = 0;
-  for (int s = 0; s < 10; ++s) {
-    if (s == 5) BHIP(b, batch_dt(st, b->desc_d, b->nruns, cfl));
-    BHIP(b, batch_stage(st, b->bl, b->budget, b->grid, b->prec, EPI_RK, cur, CK_A[s % 5],
-                        CK_B[s % 5], (s == 4 || s == 9) ? 1 : 0, s % 5 < 4));
-    cur = 1 - cur;
-  }
-  return DGX_OK;
+  dgx_status r = enqueue_step(b, st, cfl, 0, true);
+  return r == DGX_OK ? enqueue_step(b, st, cfl, 1, true) : r;
 }
 
 dgx_status ensure_graph(dgx_batch b, double cfl) {
@@ -224,9 +253,10 @@ dgx_status dgx_batch_create(const dgx_config* cfgs, int32_t nruns, void* hip_str
       b->cus < 1)
     b->cus = 256;
   bool ok = dev_alloc(b, (void**)&b->desc_d, sizeof(RunDesc) * nruns) &&
-            dev_alloc(b, (void**)&b->order_d, sizeof(int) * nruns) &&
-            dev_alloc(b, (void**)&b->prefix_d, sizeof(int) * (nruns + 1)) &&
             dev_alloc(b, (void**)&b->flag_d, sizeof(int) * 2);
+  for (int gi = 0; ok && gi < dgx_batch_s::GROUPS; ++gi)
+    ok = dev_alloc(b, (void**)&b->order_d[gi], sizeof(int) * nruns) &&
+         dev_alloc(b, (void**)&b->prefix_d[gi], sizeof(int) * (nruns + 1));
   for (int r = 0; ok && r < nruns; ++r) {
     const dgx_config& c = cfgs[r];
     const int n = c.polydeg + 1;
@@ -257,16 +287,20 @@ dgx_status dgx_batch_create(const dgx_config* cfgs, int32_t nruns, void* hip_str
     dgx_batch_destroy(b);
     return DGX_ENOMEM;
   }
-  b->order.resize(nruns);
-  for (int r = 0; r < nruns; ++r) b->order[r] = r;
-  std::stable_sort(b->order.begin(), b->order.end(),
+  std::vector<int>& all = b->order[dgx_batch_s::ALL];
+  all.resize(nruns);
+  for (int r = 0; r < nruns; ++r) all[r] = r;
+  std::stable_sort(all.begin(), all.end(),
                    [&](int x, int y) { return b->desc[x].N > b->desc[y].N; });
-  b->bl.runs = b->desc_d;
-  b->bl.order = b->order_d;
-  b->bl.prefix = b->prefix_d;
-  b->bl.nruns = nruns;
-  if (hipMemcpy(b->order_d, b->order.data(), sizeof(int) * nruns, hipMemcpyHostToDevice) != hipSuccess ||
-      upload_desc(b) != DGX_OK || set_shape(b, 256, 0) != DGX_OK) {
+  for (int r : all) {   // the kernel of a run is that of dgx_step on it (the same results)
+    const RunDesc& d = b->desc[r];
+    const bool pencil = b->prec == DGX_FP64 && batch_pencil_run(d.N, d.E, d.surf);
+    b->order[pencil ? dgx_batch_s::PENCIL + d.N - BATCH_NMIN : (int)dgx_batch_s::TILED].push_back(r);
+  }
+  bool up = upload_desc(b) == DGX_OK && set_shape(b, 256, 0) == DGX_OK;
+  for (int gi = dgx_batch_s::PENCIL; up && gi < dgx_batch_s::GROUPS; ++gi)
+    up = upload_group(b, gi, [](int N) { return batch_pencil_elems(N); }) == DGX_OK;
+  if (!up) {
     dgx_batch_destroy(b);
     return DGX_EHIP;
   }
@@ -296,7 +330,8 @@ dgx_status dgx_batch_step(dgx_batch b, double* const* u, int32_t nsteps, double 
   dgx_status st = bind(b, u, nullptr, t);
   if (st != DGX_OK) return st;
   if (nsteps == 0) return DGX_OK;
-  BHIP(b, batch_maxspeed(b->stream, b->bl, b->budget, b->grid));
+  const BatchLaunch& all = b->bl[dgx_batch_s::ALL];
+  BHIP(b, batch_maxspeed(b->stream, all, b->budget, round8(all.total)));
   int pairs = nsteps / 2;
   if (pairs > 0) {
     st = ensure_graph(b, cfl);
@@ -304,7 +339,7 @@ dgx_status dgx_batch_step(dgx_batch b, double* const* u, int32_t nsteps, double 
     for (int p = 0; p < pairs; ++p) BHIP(b, hipGraphLaunch(b->gexec, b->stream));
   }
   if (nsteps % 2) {
-    st = enqueue_step(b, b->stream, cfl, false);
+    st = enqueue_step(b, b->stream, cfl, 0, false);
     if (st != DGX_OK) return st;
     int64_t mx = 0;
     for (int64_t v : b->nodes) mx = std::max(mx, 5 * v);
@@ -323,8 +358,7 @@ dgx_status dgx_batch_rhs(dgx_batch b, const double* const* u, double* const* du)
   }
   dgx_status st = bind(b, const_cast<double* const*>(u), du, nullptr);
   if (st != DGX_OK) return st;
-  BHIP(b, batch_stage(b->stream, b->bl, b->budget, b->grid, b->prec, EPI_RHS, 0, 0.0, 0.0, 0, 0));
-  return DGX_OK;
+  return enqueue_stage(b, b->stream, EPI_RHS, 0, 0.0, 0.0, 0, 0);
 }
 
 dgx_status dgx_batch_tune(dgx_batch b, double* const* u, int32_t budget_ms) {
@@ -347,12 +381,11 @@ dgx_status dgx_batch_tune(dgx_batch b, double* const* u, int32_t budget_ms) {
       if (used > budget_ms) break;
       st = set_shape(b, budget, m ? ((b->cus * m + 7) / 8) * 8 : 0);
       if (st != DGX_OK) break;
-      const int grid = b->grid;
       float ms = 0.f, total = 0.f;
       bool fail = false;
       for (int rep = 0; rep < 4 && !fail; ++rep) {
         fail |= hipEventRecord(e0, b->stream) != hipSuccess;
-        fail |= batch_stage(b->stream, b->bl, budget, grid, b->prec, EPI_RHS, 0, 0.0, 0.0, 0, 0) != hipSuccess;
+        fail |= enqueue_stage(b, b->stream, EPI_RHS, 0, 0.0, 0.0, 0, 0) != DGX_OK;
         fail |= hipEventRecord(e1, b->stream) != hipSuccess;
         fail |= hipEventSynchronize(e1) != hipSuccess;
         fail |= hipEventElapsedTime(&ms, e0, e1) != hipSuccess;
@@ -367,7 +400,7 @@ dgx_status dgx_batch_tune(dgx_batch b, double* const* u, int32_t budget_ms) {
       if (total / 3 < best) {
         best = total / 3;
         bb = budget;
-        bg = grid;
+        bg = b->grid;
       }
     }
   }

@@ -26,10 +26,10 @@ struct RunDesc {
 
 struct BatchLaunch {
   const RunDesc* runs;
-  const int* order;     // runs sorted by polydeg (heaviest first)
+  const int* order;     // the launch's runs, sorted by polydeg (heaviest first)
   const int* prefix;    // prefix[i] = tiles of order[0..i-1]; prefix[nruns] = all tiles
   int nruns;
-  int total;            // work items = tiles of all runs
+  int total;            // work items = tiles of these runs
 };
 
 // Host launchers (batch_kernels.hip).  budget: threads per block (256 or 512); grid: number
@@ -37,6 +37,12 @@ struct BatchLaunch {
 // over them); kw: the RK stage writes k (0 in a step's last stage).
 hipError_t batch_stage(hipStream_t st, const BatchLaunch& b, int budget, int grid, int prec,
                        int epi, int cur, double A, double B, int emit_speed, int kw);
+// The same stage for runs of one polydeg large enough for a line of nodes per thread (float64;
+// use_pencil): one block per tile of batch_pencil_elems(N) elements.
+hipError_t batch_pencil_stage(hipStream_t st, const BatchLaunch& b, int N, int epi, int cur,
+                              double A, double B, int emit_speed, int kw);
+int batch_pencil_elems(int N);
+bool batch_pencil_run(int N, int64_t E, int surf);
 hipError_t batch_maxspeed(hipStream_t st, const BatchLaunch& b, int budget, int grid);
 hipError_t batch_dt(hipStream_t st, const RunDesc* runs, int nruns, double cfl);
 hipError_t batch_copy(hipStream_t st, const RunDesc* runs, int nruns, int64_t max_len);

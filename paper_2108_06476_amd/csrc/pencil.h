@@ -1,26 +1,26 @@
-// pencil.h -- the stage of 3D Cartesian elements of 4^3 nodes (N = 3) on meshes that fill the
-// chip, with one line of nodes per thread: EC flux differencing in float64, LLF or HLL
-// interface fluxes.  The same semidiscretisation as k_stage, split differently.
+// pencil.h -- the stage of 3D Cartesian elements (N = 3 to 7) on meshes that fill the chip, with
+// one line of nodes per thread: EC flux differencing in float64, LLF or HLL interface fluxes.
+// The same semidiscretisation as k_stage, split differently.
 //
-// A wave takes four elements (256 nodes, 64 lines per direction) and works through the
-// directions z, y, x; a thread holds one line's four nodes in registers.  Against k_stage's
-// one node per thread
+// A block (or wave) takes whole elements and works through the directions z, y, x; a thread
+// holds the n nodes of one line in registers.  Against k_stage's one node per thread
 //   - every pair flux of a line is formed and both its contributions added in registers: no
 //     LDS atomics, operator coefficients and series constants as scalar operands;
-//   - a line has one minus and one plus face, so the interface fluxes run with all 64 lanes
-//     (k_stage: 32 of 64 in each direction).
-// At 32^3 elements the right-hand side issues 1 738 vector instructions per four elements
-// against 3 028 in k_stage.  What bounds it then is memory: at 64^3 elements a Runge-Kutta
-// stage moves 3.1 GB (counted between the L2s and the rest, 2.4 GB algorithmic) in 600 us,
-// 5.2 TB/s of the 6.0 TB/s that a copy reaches.
+//   - a line has one minus and one plus face, so the interface fluxes run with all lanes
+//     (k_stage: 2/n of them in each direction);
+//   - elements of several waves meet at five block barriers instead of one per pair round.
+// At N = 3 and 32^3 elements the right-hand side issues 1 738 vector instructions per four
+// elements against 3 028 in k_stage.  What bounds it then is memory: at 64^3 elements a
+// Runge-Kutta stage moves 3.1 GB (counted between the L2s and the rest, 2.4 GB algorithmic) in
+// 600 us, 5.2 TB/s of the 6.0 TB/s that a copy reaches.
 //
-// The lines change lanes through LDS, 10 KB per wave: first the primitives of the home lines
-// (x), read in z and y layout; when the y lines are in registers the buffer takes the z sums,
-// then the z and y sums, on their way to the home lines.  The conserved home line stays in
-// registers (40 of 233 VGPRs) for the x primitives and the update; reading it again instead
-// cost more (64^3: 480 against 413 us per right-hand side).  Two waves per SIMD: at three
-// (168 VGPRs) the compiler spills, and even 20 spilled registers cost more than the third
-// wave gives.  Face states are loaded a direction ahead of their use.
+// The lines change threads through LDS (five planes of the block's nodes): first the primitives
+// of the home lines (x), read in z and y layout; when the y lines are in registers the buffer
+// takes the z sums, then the z and y sums, on their way to the home lines.  The conserved home
+// line stays in registers for the x primitives and the update where they allow it; reading it
+// again cost more (N = 3, 64^3: 480 against 413 us per right-hand side).  Two waves per SIMD: at
+// three (168 VGPRs, N = 3) the compiler spills, and even 20 spilled registers cost more than the
+// third wave gives.
 #pragma once
 #include <hip/hip_runtime.h>
 
@@ -35,22 +35,60 @@ __device__ __forceinline__ void phase_fence() {
   __builtin_amdgcn_sched_barrier(0);
 }
 
-constexpr int PENCIL_EW = 4;   // elements of 4^3 nodes per wave
-
-// LDS buffer of a wave: [variable][node of the wave's elements].
-struct PencilLds {
-  double q[5][64 * PENCIL_EW];   // (rho, v, E); then sums
+// The split by degree: EB elements per block (per wave, where the lines of whole elements fill
+// one), one line of a direction per thread.  Lanes without a line: none for N = 3 and 7, 2 %
+// (N = 4), 16 % (N = 5; in blocks of four waves 2 %, but 24^3 then takes 749 us per step
+// against 702: fewer, larger blocks leave more of the last round idle), 23 % (N = 6; four waves
+// 4 %, 1 406 against 1 262 us at 24^3).
+template <int N, int EPI>
+struct Pencil {
+  static_assert(N >= 3 && N <= 7, "degrees with enough pairs per line");
+  static constexpr int n = N + 1, NL = n * n, NN = n * n * n;
+  static constexpr int THREADS = N == 4 || N == 5 ? 128 : 64;
+  static constexpr bool WAVE = THREADS == 64;        // the waves of a block are independent
+  static constexpr int EB = THREADS / NL;
+  static constexpr bool FULL = EB * NL == THREADS;   // every thread has a line of its own
+  // Waves per SIMD: two (256 registers).  N = 7 time steps: one (512, half of them AGPRs that
+  // hold values), so that the conserved line stays in registers; 24^3 1 684 us per step against
+  // 1 741 with two waves that read it three times (right-hand side alone: 257 against 236).
+  static constexpr int WAVES = N == 7 && EPI == EPI_RK ? 1 : 2;
+  static constexpr bool HOLD = N != 6 && (N != 7 || EPI == EPI_RK);   // the conserved home line
+                                          // stays in registers, or is read twice again
+  static constexpr bool PRE = N <= 4 || (N == 7 && HOLD);   // faces loaded a direction ahead
+  static constexpr int ROW = N <= 4 ? n : 3;   // pairs of a row whose means are formed together
 };
 
-// Position in a plane of the buffer of node (i, j, k) of element le: i ^ 4j ^ 37k ^ 16 le_0 ^
-// 128 le_1 (a permutation of 0..255).  The 32 lanes that an 8-byte LDS access serves at a
-// time hold, for a fixed node of their lines, 32 different positions modulo 32 in all three
-// directions: no bank conflicts.  A line's node m is at base ^ (m step).
-template <int D>
-__device__ __forceinline__ int pencil_at(int base, int m) {
-  return base ^ (m * (D == 0 ? 1 : D == 1 ? 4 : 37));
+// LDS buffer: [variable][node of the block's (wave's) elements].
+template <int N>
+struct PencilLds {
+  double q[5][Pencil<N, EPI_RK>::EB * Pencil<N, EPI_RK>::NN];   // (rho, v, E); then sums
+};
+
+// Position in a plane of the buffer of node (i, j, k) of element slot le.  n = 4: i ^ 4j ^ 37k ^
+// 16 le_0 ^ 128 le_1; n = 8: i ^ 9j ^ 72k (permutations): the 32 lanes that an 8-byte LDS access
+// serves at a time hold, for a fixed node of their lines, 32 different positions modulo 32 in
+// all three directions, no bank conflicts.  Other n: the natural order (strides of 5, 6, 7
+// conflict little).  A line's node m is at base ^ (m step) or base + m step.
+template <int N>
+struct PencilPos {
+  static constexpr int n = N + 1;
+  static constexpr bool XOR = n == 4 || n == 8;
+  template <int D>
+  static __device__ __forceinline__ int at(int base, int m) {
+    if constexpr (n == 4) return base ^ (m * (D == 0 ? 1 : D == 1 ? 4 : 37));
+    else if constexpr (n == 8) return base ^ (m * (D == 0 ? 1 : D == 1 ? 9 : 72));
+    else return base + m * (D == 0 ? 1 : D == 1 ? n : n * n);
+  }
+  static __device__ __forceinline__ int elem(int le) {
+    return n == 4 ? ((le & 1) * 16) ^ ((le >> 1) * 128) : le * n * n * n;
+  }
+};
+
+template <int N>
+__device__ __forceinline__ void pencil_sync() {
+  if constexpr (Pencil<N, EPI_RK>::WAVE) wave_sync();
+  else __syncthreads();
 }
-__device__ __forceinline__ int pencil_elem(int le) { return ((le & 1) * 16) ^ ((le >> 1) * 128); }
 
 // The operator table read through the scalar cache: nothing writes it while a stage runs.
 typedef const double __attribute__((address_space(4)))* ConstTab;
@@ -69,8 +107,9 @@ __device__ __forceinline__ void st(double* base, unsigned off, int i, double v) 
 
 // A line's nodes: density, velocity (v[0] along the line, then the other two in cyclic order),
 // twice the pressure and the energy.
+template <int n>
 struct PLine {
-  double rho[4], v[3][4], p2[4], E[4];
+  double rho[n], v[3][n], p2[n], E[n];
 };
 
 // Twice the pressure from rho, v (components x, y, z: the same value whatever the line's
@@ -152,59 +191,69 @@ __device__ __forceinline__ void pencil_far(double a, double b, double c, double 
 // be: (gamma - 1) beta / 2 of the nodes.  The near-equal series serves all lanes; where a lane
 // of the wave is beyond it, the row's means are formed again one pair at a time, in a loop
 // that keeps the code and the registers of that rare path small.
-template <typename Park, typename Unpark>
-__device__ __forceinline__ void pencil_volume(PLine& q, double (&be)[4], ConstTab S, Park park,
-                                              Unpark unpark, double (&acc)[4][5]) {
-  constexpr int n = 4;
+template <int n, int ROW, typename Park, typename Unpark>
+__device__ __forceinline__ void pencil_volume(PLine<n>& q, double (&be)[n], ConstTab S, Park park,
+                                              Unpark unpark, double (&acc)[n][5]) {
   const double c1 = sconst(-1.0 / 6.0), c2 = sconst(-2.0 / 45.0), c3 = -22.0 / 945.0;
   const double e1 = sconst(2.0 / 3.0), e2 = sconst(2.0 / 5.0), e3 = 2.0 / 7.0;
 #pragma unroll
   for (int i = 0; i < n - 1; ++i) {
-    double rl[n], ib[n];   // [m]: the row's means
-    bool far = false;
 #pragma unroll
-    for (int m = i + 1; m < n; ++m) {
-      const double sr = q.rho[i] + q.rho[m], dr = q.rho[m] - q.rho[i];
-      const double zr = dr * rcp_nr1(sr), xr = zr * zr;
-      const double sb = be[i] + be[m], db = be[m] - be[i];
-      const double rb = rcp_nr1(sb);
-      const double zb = db * rb, xb = zb * zb;
-      rl[m] = sr * fma(xr, fma(xr, fma(xr, c3, c2), c1), 0.5);
-      ib[m] = rb * fma(xb, fma(xb, fma(xb, e3, e2), e1), 2.0);
-      far |= !(xr < 1.0e-4) | !(xb < 1.0e-4);
-    }
-    if (__builtin_expect(__any(far) != 0, 0)) {
-      // one pair at a time at the head of the row, whose registers rotate; park and unpark
-      // free registers meanwhile
-      park();
-#pragma unroll 1
-      for (int c = i + 1; c < n; ++c) {
-        pencil_far(q.rho[i], q.rho[i + 1], be[i], be[i + 1], rl[i + 1], ib[i + 1]);
-        const double t0 = q.rho[i + 1], t1 = be[i + 1], t2 = rl[i + 1], t3 = ib[i + 1];
+    for (int m0 = i + 1; m0 < n; m0 += ROW) {
+      const int m1 = m0 + ROW < n ? m0 + ROW : n;
+      double rl[ROW], ib[ROW];
+      bool far = false;
 #pragma unroll
-        for (int m = i + 1; m < n - 1; ++m) {
-          q.rho[m] = q.rho[m + 1];
-          be[m] = be[m + 1];
-          rl[m] = rl[m + 1];
-          ib[m] = ib[m + 1];
-        }
-        q.rho[n - 1] = t0;
-        be[n - 1] = t1;
-        rl[n - 1] = t2;
-        ib[n - 1] = t3;
+      for (int m = m0; m < m1; ++m) {
+        const double sr = q.rho[i] + q.rho[m], dr = q.rho[m] - q.rho[i];
+        const double zr = dr * rcp_nr1(sr), xr = zr * zr;
+        const double sb = be[i] + be[m], db = be[m] - be[i];
+        const double rb = rcp_nr1(sb);
+        const double zb = db * rb, xb = zb * zb;
+        rl[m - m0] = sr * fma(xr, fma(xr, fma(xr, c3, c2), c1), 0.5);
+        ib[m - m0] = rb * fma(xb, fma(xb, fma(xb, e3, e2), e1), 2.0);
+        far |= !(xr < 1.0e-4) | !(xb < 1.0e-4);
       }
-      unpark();
-    }
+      if (__builtin_expect(__any(far) != 0, 0)) {
+        // one pair at a time at the head of the chunk, whose registers rotate; park and
+        // unpark free registers meanwhile
+        park();
+#pragma unroll 1
+        for (int c = m0; c < m1; ++c) {
+          pencil_far(q.rho[i], q.rho[m0], be[i], be[m0], rl[0], ib[0]);
+          const double t0 = q.rho[m0], t1 = be[m0], t2 = rl[0], t3 = ib[0];
 #pragma unroll
-    for (int m = i + 1; m < n; ++m) {
-      double f[5];
-      pencil_pair(rl[m], ib[m], q.v[0][i], q.v[1][i], q.v[2][i], q.p2[i], q.v[0][m], q.v[1][m],
-                  q.v[2][m], q.p2[m], f);
-      const double cim = S[i * TMAX + m], cmi = S[m * TMAX + i];
+          for (int m = m0; m < m1 - 1; ++m) {
+            q.rho[m] = q.rho[m + 1];
+            be[m] = be[m + 1];
+            rl[m - m0] = rl[m - m0 + 1];
+            ib[m - m0] = ib[m - m0 + 1];
+          }
+          q.rho[m1 - 1] = t0;
+          be[m1 - 1] = t1;
+          rl[m1 - 1 - m0] = t2;
+          ib[m1 - 1 - m0] = t3;
+        }
+        unpark();
+      }
+#pragma unroll
+      for (int m = m0; m < m1; ++m) {
+        double f[5];
+        pencil_pair(rl[m - m0], ib[m - m0], q.v[0][i], q.v[1][i], q.v[2][i], q.p2[i], q.v[0][m],
+                    q.v[1][m], q.v[2][m], q.p2[m], f);
+        const double cim = S[i * TMAX + m], cmi = S[m * TMAX + i];
+#pragma unroll
+        for (int v = 0; v < 5; ++v) {
+          acc[i][v] = fma(cim, f[v], acc[i][v]);
+          acc[m][v] = fma(cmi, f[v], acc[m][v]);
+        }
+      }
+      // the sums are formed here: sunk past the next rows they would keep every flux alive
 #pragma unroll
       for (int v = 0; v < 5; ++v) {
-        acc[i][v] = fma(cim, f[v], acc[i][v]);
-        acc[m][v] = fma(cmi, f[v], acc[m][v]);
+        asm("" : "+v"(acc[i][v]));
+#pragma unroll
+        for (int m = m0; m < m1; ++m) asm("" : "+v"(acc[m][v]));
       }
     }
   }
@@ -252,14 +301,14 @@ __device__ __forceinline__ void pencil_face(const Geom& g, int surf, bool plus, 
 
 // The neighbours' face nodes of a line in direction D: at [0] across its minus end, at [1]
 // across its plus end; momentum components in the order D, D + 1, D + 2.
-template <int D>
+template <int N, int D>
 __device__ __forceinline__ void pencil_face_load(const double* __restrict__ u, const Geom& g, int e,
                                                  const int (&ec)[3], int la, int lb, size_t ENN,
                                                  double (&un)[2][5]) {
-  constexpr int n = 4, NN = 64, nd = Stride<D, n>::value;
+  constexpr int n = N + 1, NN = n * n * n, nd = Stride<D, n>::value;
   constexpr int na = D == 0 ? n : 1, nb = D == 2 ? n : n * n;
   const int nod = la * na + lb * nb;
-  const unsigned o[2] = {((unsigned)elem_nb(g, e, ec, D, -1) * NN + nod + 3 * nd) * 8u,
+  const unsigned o[2] = {((unsigned)elem_nb(g, e, ec, D, -1) * NN + nod + N * nd) * 8u,
                          ((unsigned)elem_nb(g, e, ec, D, 1) * NN + nod) * 8u};
 #pragma unroll
   for (int s = 0; s < 2; ++s) {
@@ -271,12 +320,12 @@ __device__ __forceinline__ void pencil_face_load(const double* __restrict__ u, c
 }
 
 // A line's primitives from the LDS.
-template <int D>
-__device__ __forceinline__ void pencil_read(const PencilLds& s, int bl, double gm1, PLine& q,
-                                            double (&be)[4]) {
+template <int N, int D>
+__device__ __forceinline__ void pencil_read(const PencilLds<N>& s, int bl, double gm1,
+                                            PLine<N + 1>& q, double (&be)[N + 1]) {
 #pragma unroll
-  for (int m = 0; m < 4; ++m) {
-    const int x = pencil_at<D>(bl, m);
+  for (int m = 0; m < N + 1; ++m) {
+    const int x = PencilPos<N>::template at<D>(bl, m);
     q.rho[m] = s.q[0][x];
 #pragma unroll
     for (int k = 0; k < 3; ++k) q.v[k][m] = s.q[1 + (D + k) % 3][x];
@@ -285,15 +334,16 @@ __device__ __forceinline__ void pencil_read(const PencilLds& s, int bl, double g
                         q.v[(5 - D) % 3][m], q.E[m]);
   }
 #pragma unroll
-  for (int m = 0; m < 4; ++m) be[m] = (gm1 * q.rho[m]) * rcp_nr1(q.p2[m]);
+  for (int m = 0; m < N + 1; ++m) be[m] = (gm1 * q.rho[m]) * rcp_nr1(q.p2[m]);
 }
 
 // The running sums of a line from and to the LDS (component order of the line in registers).
-template <int D>
-__device__ __forceinline__ void pencil_sums_get(const PencilLds& s, int bl, double (&acc)[4][5]) {
+template <int N, int D>
+__device__ __forceinline__ void pencil_sums_get(const PencilLds<N>& s, int bl,
+                                                double (&acc)[N + 1][5]) {
 #pragma unroll
-  for (int m = 0; m < 4; ++m) {
-    const int x = pencil_at<D>(bl, m);
+  for (int m = 0; m < N + 1; ++m) {
+    const int x = PencilPos<N>::template at<D>(bl, m);
     acc[m][0] = s.q[0][x];
 #pragma unroll
     for (int k = 0; k < 3; ++k) acc[m][1 + k] = s.q[1 + (D + k) % 3][x];
@@ -301,11 +351,12 @@ __device__ __forceinline__ void pencil_sums_get(const PencilLds& s, int bl, doub
   }
 }
 
-template <int D>
-__device__ __forceinline__ void pencil_sums_put(PencilLds& s, int bl, const double (&acc)[4][5]) {
+template <int N, int D>
+__device__ __forceinline__ void pencil_sums_put(PencilLds<N>& s, int bl,
+                                                const double (&acc)[N + 1][5]) {
 #pragma unroll
-  for (int m = 0; m < 4; ++m) {
-    const int x = pencil_at<D>(bl, m);
+  for (int m = 0; m < N + 1; ++m) {
+    const int x = PencilPos<N>::template at<D>(bl, m);
     s.q[0][x] = acc[m][0];
 #pragma unroll
     for (int k = 0; k < 3; ++k) s.q[1 + (D + k) % 3][x] = acc[m][1 + k];
@@ -313,13 +364,13 @@ __device__ __forceinline__ void pencil_sums_put(PencilLds& s, int bl, const doub
   }
 }
 
-template <int D>
+template <int N, int D>
 __device__ __forceinline__ void pencil_faces(const Geom& g, int surf, ConstTab tab,
-                                             const PLine& q, const double (&un)[2][5],
+                                             const PLine<N + 1>& q, const double (&un)[2][5],
                                              double (&f)[2][5]) {
   pencil_face(g, surf, false, q.rho[0], q.v[0][0], q.v[1][0], q.v[2][0], q.p2[0], q.E[0], un[0],
               tab[TAB_LIFT + 2 * D], f[0]);
-  pencil_face(g, surf, true, q.rho[3], q.v[0][3], q.v[1][3], q.v[2][3], q.p2[3], q.E[3], un[1],
+  pencil_face(g, surf, true, q.rho[N], q.v[0][N], q.v[1][N], q.v[2][N], q.p2[N], q.E[N], un[1],
               tab[TAB_LIFT + 2 * D + 1], f[1]);
 }
 
@@ -331,30 +382,42 @@ __device__ __forceinline__ double row_max16(double x) {
   return fmax(x, dpp_f64<0x140, 0xF>(x, x));
 }
 
-template <int EPI>
-__device__ __forceinline__ void pencil_tile(PencilLds& s, const StageArgs& a, const Geom& g,
+template <int N, int EPI>
+__device__ __forceinline__ void pencil_tile(PencilLds<N>& s, const StageArgs& a, const Geom& g,
                                             int tile) {
-  constexpr int n = 4, NN = 64;
-  const int lane = (int)(threadIdx.x & 63u);
-  const int le = lane >> 4, line = lane & 15;
-  const int la = line & 3, lb = line >> 2;   // the line's place in the other two directions
-  const int er = tile * PENCIL_EW + le;
-  const bool on = er < g.E;
-  const int e = on ? er : (int)g.E - 1;      // lanes beyond the mesh repeat its last element
+  using P = Pencil<N, EPI>;
+  using X = PencilPos<N>;
+  constexpr int n = P::n, NL = P::NL, NN = P::NN;
+  const int t = P::WAVE ? (int)(threadIdx.x & 63u) : (int)threadIdx.x;
+  // threads beyond the block's lines repeat its last line, lanes beyond the mesh its last element
+  const bool own = P::FULL || t < P::EB * NL;
+  const int tl = own ? t : P::EB * NL - 1;
+  const int le = tl / NL, line = tl - le * NL;
+  const int lb = line / n, la = line - lb * n;   // the line's place in the other two directions
+  const int er = tile * P::EB + le;
+  const bool on = own && er < g.E;
+  const int e = er < g.E ? er : (int)g.E - 1;
   const size_t ENN = (size_t)g.E * NN;
   const ConstTab tab = const_tab(g.tab);
   const double gm1 = g.gamma - 1.0;
   int ec[3];
   elem_xyz(g, e, ec);
-  const unsigned ho = ((unsigned)e * NN + line * n) * 8u;   // home: the x line (j, k) = (la, lb)
-  const int eb = pencil_elem(le);
-  const int bx = pencil_at<2>(pencil_at<1>(eb, la), lb);
-  const int by = pencil_at<2>(pencil_at<0>(eb, la), lb);
-  const int bz = pencil_at<1>(pencil_at<0>(eb, la), lb);
+  unsigned ho = ((unsigned)e * NN + line * n) * 8u;   // home: the x line (j, k) = (la, lb)
+  const int eb = X::elem(le);
+  const int bx = X::template at<2>(X::template at<1>(eb, la), lb);
+  const int by = X::template at<2>(X::template at<0>(eb, la), lb);
+  const int bz = X::template at<1>(X::template at<0>(eb, la), lb);
 
-  double um[5][n], un[2][5], acc[n][5];
+  double um[5][n], un[2][5], unb[2][5], f[2][5], acc[n][5], be[n];
+  PLine<n> q;
+  auto load_u = [&]() {
+#pragma unroll
+    for (int v = 0; v < 5; ++v)
+#pragma unroll
+      for (int i = 0; i < n; ++i) um[v][i] = ld(a.uin + v * ENN, ho, i);
+  };
   // conserved -> primitive of the home line
-  auto prims = [&](PLine& q) {
+  auto prims = [&]() {
     bool ok = true;
 #pragma unroll
     for (int i = 0; i < n; ++i) {
@@ -368,93 +431,78 @@ __device__ __forceinline__ void pencil_tile(PencilLds& s, const StageArgs& a, co
     }
     return ok;
   };
-#pragma unroll
-  for (int v = 0; v < 5; ++v)
-#pragma unroll
-    for (int i = 0; i < n; ++i) um[v][i] = ld(a.uin + v * ENN, ho, i);
-  // the line's sums into the lane's part of the LDS buffer and back, where the buffer is free
-  double* const pk = &s.q[0][0] + (threadIdx.x & 63u);
-  auto park = [&]() {
-#pragma unroll
-    for (int m = 0; m < n; ++m)
-#pragma unroll
-      for (int v = 0; v < 5; ++v) pk[(m * 5 + v) * 64] = acc[m][v];
-  };
-  auto unpark = [&]() {
-#pragma unroll
-    for (int m = 0; m < n; ++m)
-#pragma unroll
-      for (int v = 0; v < 5; ++v) acc[m][v] = pk[(m * 5 + v) * 64];
-  };
-  double f[2][5], unb[2][5];
-  PLine q;
-  double be[n];
-  pencil_face_load<2>(a.uin, g, e, ec, la, lb, ENN, un);
-  pencil_face_load<1>(a.uin, g, e, ec, la, lb, ENN, unb);
-  if (!prims(q)) *g.flag = 1;
+  load_u();
+  pencil_face_load<N, 2>(a.uin, g, e, ec, la, lb, ENN, un);
+  if constexpr (P::PRE) pencil_face_load<N, 1>(a.uin, g, e, ec, la, lb, ENN, unb);
+  if (!prims()) *g.flag = 1;
 #pragma unroll
   for (int i = 0; i < n; ++i) {
-    const int x = pencil_at<0>(bx, i);
+    const int x = X::template at<0>(bx, i);
     s.q[0][x] = q.rho[i];
 #pragma unroll
     for (int k = 0; k < 3; ++k) s.q[1 + k][x] = q.v[k][i];
     s.q[4][x] = q.E[i];
   }
-  wave_sync();
-  pencil_read<2>(s, bz, gm1, q, be);
-  pencil_faces<2>(g, a.surf, tab, q, un, f);
+  pencil_sync<N>();
+
+  // ---- z
+  pencil_read<N, 2>(s, bz, gm1, q, be);
+  pencil_faces<N, 2>(g, a.surf, tab, q, un, f);
 #pragma unroll
   for (int m = 0; m < n; ++m)
 #pragma unroll
-    for (int v = 0; v < 5; ++v) acc[m][v] = m == 0 ? f[0][v] : m == 3 ? f[1][v] : 0.0;
+    for (int v = 0; v < 5; ++v) acc[m][v] = m == 0 ? f[0][v] : m == N ? f[1][v] : 0.0;
   phase_fence();
-  pencil_face_load<0>(a.uin, g, e, ec, la, lb, ENN, un);
+  if constexpr (P::PRE) pencil_face_load<N, 0>(a.uin, g, e, ec, la, lb, ENN, un);
   phase_fence();
-  // the buffer still holds the primitives here: v and p are read again instead
-  auto reread = [&]() {
-#pragma unroll
-    for (int m = 0; m < n; ++m) {
-      const int x = pencil_at<2>(bz, m);
-#pragma unroll
-      for (int k = 0; k < 3; ++k) q.v[k][m] = s.q[1 + (2 + k) % 3][x];
-      q.p2[m] = pencil_p2(gm1, s.q[0][x], s.q[1][x], s.q[2][x], s.q[3][x], s.q[4][x]);
-    }
-  };
-  pencil_volume(q, be, tab + TAB_S + 2 * TMAX * TMAX, []() {}, reread, acc);
+  pencil_volume<n, P::ROW>(q, be, tab + TAB_S + 2 * TMAX * TMAX, []() {}, []() {}, acc);
   phase_fence();
-  pencil_read<1>(s, by, gm1, q, be);
-  wave_sync();
-  pencil_sums_put<2>(s, bz, acc);
-  wave_sync();
-  pencil_faces<1>(g, a.surf, tab, q, unb, f);
+
+  // ---- y: once its lines are in registers the buffer takes the sums
+  if constexpr (!P::PRE) pencil_face_load<N, 1>(a.uin, g, e, ec, la, lb, ENN, unb);
+  pencil_read<N, 1>(s, by, gm1, q, be);
+  pencil_sync<N>();
+  pencil_sums_put<N, 2>(s, bz, acc);
+  pencil_sync<N>();
+  pencil_faces<N, 1>(g, a.surf, tab, q, unb, f);
   phase_fence();
-  pencil_sums_get<1>(s, by, acc);
+  pencil_sums_get<N, 1>(s, by, acc);
 #pragma unroll
   for (int v = 0; v < 5; ++v) {
     acc[0][v] += f[0][v];
-    acc[3][v] += f[1][v];
+    acc[N][v] += f[1][v];
   }
-  pencil_volume(q, be, tab + TAB_S + 1 * TMAX * TMAX, park, unpark, acc);
+  // (a far row's sums wait at their places in the buffer)
+  pencil_volume<n, P::ROW>(q, be, tab + TAB_S + 1 * TMAX * TMAX,
+                   [&]() { pencil_sums_put<N, 1>(s, by, acc); },
+                   [&]() { pencil_sums_get<N, 1>(s, by, acc); }, acc);
   phase_fence();
-  wave_sync();
-  pencil_sums_put<1>(s, by, acc);
-  wave_sync();
+  if constexpr (!P::HOLD) load_u();
+  if constexpr (!P::PRE) pencil_face_load<N, 0>(a.uin, g, e, ec, la, lb, ENN, un);
+  pencil_sync<N>();
+  pencil_sums_put<N, 1>(s, by, acc);
+  pencil_sync<N>();
+
+  // ---- x
+  if constexpr (P::HOLD) {
 #pragma unroll
-  for (int v = 0; v < 5; ++v)   // the primitives are formed again: held from the start they
-#pragma unroll                  // would cost 32 registers through the other directions
-    for (int i = 0; i < n; ++i) asm("" : "+v"(um[v][i]));
-  (void)prims(q);
-  pencil_faces<0>(g, a.surf, tab, q, un, f);
+    for (int v = 0; v < 5; ++v)   // the primitives are formed again: held from the start they
+#pragma unroll                    // would cost 32 registers through the other directions
+      for (int i = 0; i < n; ++i) asm("" : "+v"(um[v][i]));
+  }
+  (void)prims();
+  pencil_faces<N, 0>(g, a.surf, tab, q, un, f);
   phase_fence();
 #pragma unroll
   for (int m = 0; m < n; ++m) be[m] = (gm1 * q.rho[m]) * rcp_nr1(q.p2[m]);
-  pencil_sums_get<0>(s, bx, acc);
+  pencil_sums_get<N, 0>(s, bx, acc);
 #pragma unroll
   for (int v = 0; v < 5; ++v) {
     acc[0][v] += f[0][v];
-    acc[3][v] += f[1][v];
+    acc[N][v] += f[1][v];
   }
-  pencil_volume(q, be, tab + TAB_S, park, unpark, acc);
+  pencil_volume<n, P::ROW>(q, be, tab + TAB_S, [&]() { pencil_sums_put<N, 0>(s, bx, acc); },
+                   [&]() { pencil_sums_get<N, 0>(s, bx, acc); }, acc);
   phase_fence();
 
   // epilogue: acc[i][v] holds twice (v = 0) and four times the home line's right-hand side
@@ -466,13 +514,17 @@ __device__ __forceinline__ void pencil_tile(PencilLds& s, const StageArgs& a, co
         for (int i = 0; i < n; ++i) st(a.du + v * ENN, ho, i, (v == 0 ? 0.5 : 0.25) * acc[i][v]);
     }
   } else {
+    const double dt = a.dt_from ? stage_dt_from_partials(a) : *a.dt;
+    const double dh = 0.5 * dt, dq = 0.25 * dt;
+    if constexpr (!P::HOLD) {
+      asm("" : "+v"(ho));
+      load_u();
+    }
     double kv[5][n];
 #pragma unroll
     for (int v = 0; v < 5; ++v)
 #pragma unroll
       for (int i = 0; i < n; ++i) kv[v][i] = a.A != 0.0 ? ld(a.k + v * ENN, ho, i) : 0.0;
-    const double dt = a.dt_from ? stage_dt_from_partials(a) : *a.dt;
-    const double dh = 0.5 * dt, dq = 0.25 * dt;
     if (on) {
 #pragma unroll
       for (int v = 0; v < 5; ++v) {
@@ -496,19 +548,42 @@ __device__ __forceinline__ void pencil_tile(PencilLds& s, const StageArgs& a, co
 #pragma unroll
       for (int i = 0; i < n; ++i) {
         const double u5[5] = {um[0][i], um[1][i], um[2][i], um[3][i], um[4][i]};
-        Prim<double> q;
-        ok &= cons_to_prim<3, false>(u5, g.gamma, q);
+        Prim<double> w;
+        ok &= cons_to_prim<3, false>(u5, g.gamma, w);
 #pragma unroll
-        for (int d = 0; d < 3; ++d) l[d] = fmax(l[d], fabs(q.v[d]) + q.c);
+        for (int d = 0; d < 3; ++d) l[d] = fmax(l[d], fabs(w.v[d]) + w.c);
       }
       if (on && !ok) *g.flag = 1;
-      double lam = 0.0;   // every lane of an element's row: the element's wave speed
+      double lam = 0.0;   // the element's wave speed, in the thread that writes it
+      if constexpr (NL == 16) {
 #pragma unroll
-      for (int d = 0; d < 3; ++d) lam += tab[TAB_JAC + d] * row_max16(l[d]);
-      if (a.speed_slots) {   // one atomic per wave
-        const double w = wave_max_lane63(on ? lam : 0.0);
-        if (lane == 63) slot_max(a.speed_slots, tile, w);
-      } else if (on && line == 0) {
+        for (int d = 0; d < 3; ++d) lam += tab[TAB_JAC + d] * row_max16(l[d]);
+      } else if constexpr (NL == 64) {
+#pragma unroll
+        for (int d = 0; d < 3; ++d) lam += tab[TAB_JAC + d] * wave_max_lane63(l[d]);
+      } else {   // maxima of non-negative doubles as integers, in the buffer
+        unsigned long long* const mx = reinterpret_cast<unsigned long long*>(&s.q[0][0]);
+        pencil_sync<N>();
+        if (line < 3) mx[le * 3 + line] = 0;
+        pencil_sync<N>();
+#pragma unroll
+        for (int d = 0; d < 3; ++d)
+          if (on && l[d] > 0.0)
+            __hip_atomic_fetch_max(&mx[le * 3 + d], (unsigned long long)__double_as_longlong(l[d]),
+                                   __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        pencil_sync<N>();
+#pragma unroll
+        for (int d = 0; d < 3; ++d)
+          lam += tab[TAB_JAC + d] * __longlong_as_double((long long)mx[le * 3 + d]);
+      }
+      if (a.speed_slots) {
+        if constexpr (NL == 16) {   // one atomic per wave
+          const double w = wave_max_lane63(on ? lam : 0.0);
+          if (t == 63) slot_max(a.speed_slots, tile, w);
+        } else if (on && line == (NL == 64 ? 63 : 0)) {
+          slot_max(a.speed_slots, e, lam);
+        }
+      } else if (on && line == (NL == 64 ? 63 : 0)) {
         a.speed[e] = lam;
       }
     }
@@ -518,30 +593,36 @@ __device__ __forceinline__ void pencil_tile(PencilLds& s, const StageArgs& a, co
   }
 }
 
-// Meshes of k_pencil.  A wave carries four elements, so a mesh needs many more elements than
-// the 8 192 that its 2 048 resident waves (two per SIMD) hold at a time for the last round of
-// waves not to matter.  TGV, microseconds per step, k_stage against k_pencil: 20^3 115 / 110
-// (one full round), 24^3 176 / 181 (1.7 rounds), 28^3 264 / 261, 32^3 379 / 342, 64^3 3 590 /
-// 3 040; right-hand sides 28^3 43 / 36, 32^3 61 / 50, 64^3 525 / 402.  Upper limit: byte
-// offsets into a plane stay below 2^31 (k_stage's are 64 bits).
-constexpr int64_t PENCIL_MIN_E = 20480, PENCIL_MAX_E = (int64_t)1 << 22;
-// Four waves per block (x neighbours share an L1: 64^3 3 040 us per step, against 3 240 with
-// one) from here on; below, single-wave blocks even out the last round (32^3: 342 against 358).
+// Meshes of k_pencil, by degree: below them a mesh has too few waves for the 2 048 that are
+// resident at a time (two per SIMD), and k_stage, with four to eight times as many, is the
+// faster.  TGV, microseconds per step, k_stage against k_pencil:
+//   N = 3: 24^3 176 / 181 (1.7 rounds of waves), 28^3 264 / 261, 32^3 382 / 328, 64^3 3 525 / 3 049
+//   N = 4: 20^3 219 / 236, 24^3 370 / 346, 40^3 1 808 / 1 700
+//   N = 5: 16^3 237 / 255, 19 x 23 x 13 320 / 301, 24^3 792 / 702, 36^3 2 613 / 2 238
+//   N = 6: 8^3 79 / 118, 10^3 173 / 152, 12^3 260 / 217, 24^3 1 857 / 1 262
+//   N = 7: 16^3 508 / 547, 24^3 1 824 / 1 684
+// Upper limit: byte offsets into a plane stay below 2^31 (k_stage's are 64 bits).
+inline bool use_pencil(int N, int64_t E, int surf) {
+  constexpr int64_t min_E[5] = {20480, 12288, 5120, 960, 8192};   // N = 3..7
+  if (N < 3 || N > 7 || (surf != SURF_LLF && surf != SURF_HLL)) return false;
+  const int64_t nn = (int64_t)(N + 1) * (N + 1) * (N + 1);
+  return E >= min_E[N - 3] && E * nn <= ((int64_t)1 << 28);
+}
+// Four waves per block (x neighbours share an L1: N = 3, 64^3 3 040 us per step, against 3 240
+// with one) from here on; below, single-wave blocks even out the last round (32^3: 342 / 358).
 constexpr int64_t PENCIL_WIDE_E = 40960;
 
-inline bool use_pencil(int64_t E, int surf) {
-  return E >= PENCIL_MIN_E && E < PENCIL_MAX_E && (surf == SURF_LLF || surf == SURF_HLL);
-}
-
-// The waves of a block are independent (no block barrier).
-template <int EPI, int WPB>
-__global__ __launch_bounds__(64 * WPB) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_pencil(
-    StageArgs a, Geom g) {
-  __shared__ PencilLds s[WPB];
-  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+// WPB: independent waves per block where a wave holds its elements whole, else 1.
+template <int N, int EPI, int WPB>
+__global__ __launch_bounds__((Pencil<N, EPI>::THREADS * WPB))
+__attribute__((amdgpu_waves_per_eu((Pencil<N, EPI>::WAVES), (Pencil<N, EPI>::WAVES))))
+void k_pencil(StageArgs a, Geom g) {
+  using P = Pencil<N, EPI>;
+  __shared__ PencilLds<N> s[WPB];
+  const int w = P::WAVE ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) : 0;
   const int tile = (int)xcd_tile(blockIdx.x, gridDim.x) * WPB + w;
-  if ((int64_t)tile * PENCIL_EW >= g.E) return;
-  pencil_tile<EPI>(s[w], a, g, tile);
+  if ((int64_t)tile * P::EB >= g.E) return;   // (whole waves; the last block starts inside)
+  pencil_tile<N, EPI>(s[w], a, g, tile);
 }
 
 }  // namespace dgx

@@ -74,9 +74,9 @@ struct Launch {
 
   template <int EPI, int WPB>
   static hipError_t pencil1(hipStream_t st, const StageArgs& a, const Geom& g) {
-    constexpr int per = PENCIL_EW * WPB;   // elements per block
-    hipLaunchKernelGGL((k_pencil<EPI, WPB>), dim3((unsigned)((g.E + per - 1) / per)),
-                       dim3(64 * WPB), 0, st, a, g);
+    constexpr int per = Pencil<N, EPI>::EB * WPB;   // elements per block
+    hipLaunchKernelGGL((k_pencil<N, EPI, WPB>), dim3((unsigned)((g.E + per - 1) / per)),
+                       dim3(Pencil<N, EPI>::THREADS * WPB), 0, st, a, g);
     return hipGetLastError();
   }
 
@@ -84,9 +84,11 @@ struct Launch {
   static hipError_t stage_epi(hipStream_t st, const StageArgs& a, const Geom& g, int vol, int prec) {
     if (vol == VOL_EC) {
       if (prec == PREC_MIXED) return stage1<VOL_EC, EPI, float>(st, a, g);
-      if constexpr (DIM == 3 && N == 3) {
-        if (use_pencil(g.E, a.surf)) {
-          if (g.E >= PENCIL_WIDE_E) return pencil1<EPI, 4>(st, a, g);
+      if constexpr (DIM == 3 && N >= 3) {
+        if (use_pencil(N, g.E, a.surf)) {
+          if constexpr (N == 3) {
+            if (g.E >= PENCIL_WIDE_E) return pencil1<EPI, 4>(st, a, g);
+          }
           return pencil1<EPI, 1>(st, a, g);
         }
       }
