@@ -464,6 +464,8 @@ dgx_status enqueue_step(dgx_handle h, double* const (&buf)[2], int& cur, double 
       if (slots) a.slots_clear = h->slots;   // read by stage 0, written again by stage 4
     }
     a.kw = st < 4;
+    a.nt_out = stream_output(state_bytes(h),
+                             h->curved ? 13 * sizeof(double) * (size_t)h->E * h->NN : 0);
     // the stages of one step run back to back (an indicator kernel only precedes stage 0)
     HIPCHK(h, launch_stage(h, a, EPI_RK, st == 4));
     cur = 1 - cur;

@@ -287,6 +287,9 @@ dgx_status dgx_batch_create(const dgx_config* cfgs, int32_t nruns, void* hip_str
     dgx_batch_destroy(b);
     return DGX_ENOMEM;
   }
+  size_t state = 0;
+  for (int64_t m : b->nodes) state += sizeof(double) * 5 * (size_t)m;
+  for (RunDesc& d : b->desc) d.nt_out = stream_output(state, 0);
   std::vector<int>& all = b->order[dgx_batch_s::ALL];
   all.resize(nruns);
   for (int r = 0; r < nruns; ++r) all[r] = r;

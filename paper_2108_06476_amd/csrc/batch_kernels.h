@@ -22,6 +22,7 @@ struct RunDesc {
   int* flag;            // non-physical-state flag (shared by the batch)
   double gamma, inv_gm1;   // inv_gm1 = 1/(gamma - 1)
   int E, K[3], N, surf;
+  int nt_out;           // stream_output over the states of all runs
 };
 
 struct BatchLaunch {

@@ -64,6 +64,7 @@ __device__ __forceinline__ StageArgs run_args(const RunDesc& d, int cur, double 
   a.surf = d.surf;
   a.fvf = SURF_LLF;
   a.kw = kw;
+  a.nt_out = d.nt_out;
   return a;
 }
 

@@ -10,6 +10,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "physics.h"
 
 namespace dgx {
@@ -504,6 +506,8 @@ struct StageArgs {
   // RK: write k (0 in a step's last stage: k is dead until the next step's first stage,
   // which does not read it)
   int kw = 1;
+  // RK: store uout past the last-level cache (stream_output)
+  int nt_out = 0;
   // shock capturing, RK: the raw indicator of the stage's output state (nullptr: skip) and
   // its constants (threshold, sharpness, alpha_min, alpha_max)
   double* alpha_next = nullptr;
@@ -533,6 +537,43 @@ struct StageArgs {
   double* t0_pub = nullptr;
   int t_step = 0;
 };
+
+// An RK stage's output is read next by the following stage, after three arrays of a state's
+// size have passed.  Where these exceed the 256 MB last-level cache the output only pushes out
+// what the stage still reads: non-temporal stores leave that there.  Microseconds per step,
+// plain / non-temporal, with the bytes of the three arrays:
+//   k_pencil N = 3:  32^3 252 MB 331 / 405,  34^3 302 MB 503 / 476,  36^3 586 / 539,
+//                    64^3 3 099 / 3 016;  N = 4 32^3 918 / 862;  N = 5 24^3 674 / 655
+//   k_stage mixed:   33^3 276 MB 454 / 469,  36^3 630 / 606,  64^3 3 508 / 3 459
+//   shock capturing: 33^3 276 MB 672 / 680,  34^3 302 MB 728 / 715,  36^3 826 / 802
+//   ideal MHD N = 3: 27^3 272 MB equal, 28^3 303 MB 446 / 474, 30^3 373 MB 616 / 582,
+//                    32^3 734 / 697
+// so the line is drawn at 310 MB.  A curvilinear stage's metric (13 doubles per node, read once)
+// passes as well, and the line lies lower: 24^3 106 + 92 MB equal, 27^3 151 + 131 MB 411 / 385,
+// 28^3 465 / 442, 32^3 705 / 695.  The RK register stays plain: non-temporal as well it cost
+// up to 10 %.
+inline int stream_output(size_t state_bytes, size_t metric_bytes) {
+  return 3 * state_bytes + metric_bytes > (metric_bytes ? (size_t)256 << 20 : (size_t)310000000);
+}
+// store(v, nt) for v in [0, NV): one uniform branch.  (The empty asm on one side keeps the
+// compiler from merging the two sides' stores, which would drop the non-temporal hint.)
+template <int NV, typename Store>
+__device__ __forceinline__ void store_out(int nt, Store store) {
+  if (nt) {
+    asm volatile("" ::: "memory");
+#pragma unroll
+    for (int v = 0; v < NV; ++v) store(v, std::true_type());
+    asm volatile("" ::: "memory");
+  } else {
+#pragma unroll
+    for (int v = 0; v < NV; ++v) store(v, std::false_type());
+  }
+}
+template <typename NT>
+__device__ __forceinline__ void store_one(double* p, double v, NT) {
+  if constexpr (NT::value) __builtin_nontemporal_store(v, p);
+  else *p = v;
+}
 
 // The wave-speed slots of StageArgs::speed_slots: DT_SLOTS maxima, DT_SLOT_STRIDE doubles
 // (512 B) apart so that the atomics of different slots spread over the memory channels.
@@ -662,7 +703,9 @@ __device__ __forceinline__ void weak_dir(const L& s, int base, int node, const d
 // xb: the block's per-element LDS slots (elements of several waves reduce through them).
 // DTF: the caller may ask for the first stage's dt to be derived here (a.dt_from) and for
 // the last stage's wave speeds to be folded into slots (a.speed_slots).
-template <int DIM, int N, int NV, int EPI, int BUDGET, typename SpeedFn, bool DTF = false>
+// STREAM: uout may go past the cache (a.nt_out).
+template <int DIM, int N, int NV, int EPI, int BUDGET, typename SpeedFn, bool DTF = false,
+          bool STREAM = true>
 __device__ __forceinline__ double stage_epilogue(unsigned char* xb, const StageArgs& a,
                                                const Geom& g, int le, int node, int e, bool inb,
                                                bool active, size_t ENN, size_t own_ix,
@@ -705,9 +748,13 @@ __device__ __forceinline__ double stage_epilogue(unsigned char* xb, const StageA
         const size_t pb = (size_t)(own_ix - node) + (size_t)v * ENN;   // uniform plane base
         if (a.kw) a.k[pb + (unsigned)node] = kv[v];
         un[v] = um[v] + a.B * kv[v];
-        a.uout[pb + (unsigned)node] = un[v];
+        if constexpr (!STREAM) a.uout[pb + (unsigned)node] = un[v];
         if (un_out) un_out[v] = un[v];
       }
+      if constexpr (STREAM)
+        store_out<NV>(a.nt_out, [&](int v, auto nt) {
+          store_one(a.uout + (size_t)(own_ix - node) + (size_t)v * ENN + (unsigned)node, un[v], nt);
+        });
     }
     double* const slots = DTF ? a.speed_slots : nullptr;
     if (a.speed != nullptr || slots != nullptr) {
@@ -1061,7 +1108,10 @@ __device__ __forceinline__ void stage_tile(typename StageLdsOf<DIM, N, VOL, RT, 
         for (int d = 0; d < DIM; ++d) ls[d] = sT[TAB_JAC + d] * (fabs(q.v[d]) + q.c);
         return ok;
       };
-  const double dt_used = stage_epilogue<DIM, N, NV, EPI, BUDGET, decltype(speeds), true>(
+  // The float64 flux-differencing kernels of N >= 3 serve the meshes below use_pencil's line,
+  // which fit the cache; the branch of the streaming store costs them 3 % (8^3 to 10^3).
+  constexpr bool STREAM = !(VOL == VOL_EC && sizeof(RT) == 8 && (DIM == 2 || N >= 3));
+  const double dt_used = stage_epilogue<DIM, N, NV, EPI, BUDGET, decltype(speeds), true, STREAM>(
       s.xb, a, g, le, node, e, inb, active, ENN, own_ix, um, R, speeds, IND ? un : nullptr);
   // shock capturing: the raw indicator of the state just written, for the next stage (the
   // computation of k_indicator on the same values, in the element's LDS slot)

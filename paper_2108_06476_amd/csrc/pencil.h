@@ -40,14 +40,18 @@ __device__ __forceinline__ void phase_fence() {
 // (N = 4), 16 % (N = 5; in blocks of four waves 2 %, but 24^3 then takes 749 us per step
 // against 702: fewer, larger blocks leave more of the last round idle), 23 % (N = 6; four waves
 // 4 %, 1 406 against 1 262 us at 24^3).
-template <int N, int EPI>
-struct Pencil {
-  static_assert(N >= 3 && N <= 7, "degrees with enough pairs per line");
+template <int N>
+struct PencilMap {
   static constexpr int n = N + 1, NL = n * n, NN = n * n * n;
   static constexpr int THREADS = N == 4 || N == 5 ? 128 : 64;
   static constexpr bool WAVE = THREADS == 64;        // the waves of a block are independent
   static constexpr int EB = THREADS / NL;
   static constexpr bool FULL = EB * NL == THREADS;   // every thread has a line of its own
+};
+
+template <int N, int EPI>
+struct Pencil : PencilMap<N> {
+  static_assert(N >= 3 && N <= 7, "degrees with enough pairs per line");
   // Waves per SIMD: two (256 registers).  N = 7 time steps: one (512, half of them AGPRs that
   // hold values), so that the conserved line stays in registers; 24^3 1 684 us per step against
   // 1 741 with two waves that read it three times (right-hand side alone: 257 against 236).
@@ -55,13 +59,13 @@ struct Pencil {
   static constexpr bool HOLD = N != 6 && (N != 7 || EPI == EPI_RK);   // the conserved home line
                                           // stays in registers, or is read twice again
   static constexpr bool PRE = N <= 4 || (N == 7 && HOLD);   // faces loaded a direction ahead
-  static constexpr int ROW = N <= 4 ? n : 3;   // pairs of a row whose means are formed together
+  static constexpr int ROW = N <= 4 ? N + 1 : 3;   // pairs of a row whose means are formed together
 };
 
 // LDS buffer: [variable][node of the block's (wave's) elements].
 template <int N>
 struct PencilLds {
-  double q[5][Pencil<N, EPI_RK>::EB * Pencil<N, EPI_RK>::NN];   // (rho, v, E); then sums
+  double q[5][PencilMap<N>::EB * PencilMap<N>::NN];   // (rho, v, E); then sums
 };
 
 // Position in a plane of the buffer of node (i, j, k) of element slot le.  n = 4: i ^ 4j ^ 37k ^
@@ -84,9 +88,41 @@ struct PencilPos {
   }
 };
 
+// A thread's place in its tile.  Threads beyond the tile's lines repeat its last line, lanes
+// beyond the mesh its last element (on: neither).
+template <int N>
+struct PencilPlace {
+  int t, le, line, la, lb;   // la, lb: the line's place in the other two directions
+  int e, ec[3];
+  bool on;
+  unsigned ho;               // byte offset of the home line (x line (j, k) = (la, lb)) in a plane
+  int bx, by, bz;            // LDS positions of the thread's x, y and z lines
+
+  __device__ __forceinline__ PencilPlace(const Geom& g, int tile) {
+    using P = PencilMap<N>;
+    using X = PencilPos<N>;
+    t = P::WAVE ? (int)(threadIdx.x & 63u) : (int)threadIdx.x;
+    const bool own = P::FULL || t < P::EB * P::NL;
+    const int tl = own ? t : P::EB * P::NL - 1;
+    le = tl / P::NL;
+    line = tl - le * P::NL;
+    lb = line / P::n;
+    la = line - lb * P::n;
+    const int er = tile * P::EB + le;
+    on = own && er < g.E;
+    e = er < g.E ? er : (int)g.E - 1;
+    elem_xyz(g, e, ec);
+    ho = ((unsigned)e * P::NN + line * P::n) * 8u;
+    const int eb = X::elem(le);
+    bx = X::template at<2>(X::template at<1>(eb, la), lb);
+    by = X::template at<2>(X::template at<0>(eb, la), lb);
+    bz = X::template at<1>(X::template at<0>(eb, la), lb);
+  }
+};
+
 template <int N>
 __device__ __forceinline__ void pencil_sync() {
-  if constexpr (Pencil<N, EPI_RK>::WAVE) wave_sync();
+  if constexpr (PencilMap<N>::WAVE) wave_sync();
   else __syncthreads();
 }
 
@@ -107,6 +143,11 @@ __device__ __forceinline__ void st(double* base, unsigned off, int i, double v) 
 
 // A line's nodes: density, velocity (v[0] along the line, then the other two in cyclic order),
 // twice the pressure and the energy.
+template <typename NT>
+__device__ __forceinline__ void st_out(double* base, unsigned off, int i, double v, NT nt) {
+  store_one(reinterpret_cast<double*>(reinterpret_cast<char*>(base) + off) + i, v, nt);
+}
+
 template <int n>
 struct PLine {
   double rho[n], v[3][n], p2[n], E[n];
@@ -382,31 +423,53 @@ __device__ __forceinline__ double row_max16(double x) {
   return fmax(x, dpp_f64<0x140, 0xF>(x, x));
 }
 
+// sum_d (2/h_d) max over the element's lines of l_d, in the thread that writes it: line 0, or 63
+// of 64.  buf: LDS that is free by now (unused for N = 3 and 7).
+template <int N>
+__device__ __forceinline__ double pencil_elem_speed(double* buf, ConstTab tab,
+                                                    const PencilPlace<N>& w,
+                                                    const double (&l)[3]) {
+  constexpr int NL = PencilMap<N>::NL;
+  double lam = 0.0;
+  if constexpr (NL == 16) {
+#pragma unroll
+    for (int d = 0; d < 3; ++d) lam += tab[TAB_JAC + d] * row_max16(l[d]);
+  } else if constexpr (NL == 64) {
+#pragma unroll
+    for (int d = 0; d < 3; ++d) lam += tab[TAB_JAC + d] * wave_max_lane63(l[d]);
+  } else {   // maxima of non-negative doubles as integers
+    unsigned long long* const mx = reinterpret_cast<unsigned long long*>(buf) + w.le * 3;
+    pencil_sync<N>();
+    if (w.line < 3) mx[w.line] = 0;
+    pencil_sync<N>();
+#pragma unroll
+    for (int d = 0; d < 3; ++d)
+      if (w.on && l[d] > 0.0)
+        __hip_atomic_fetch_max(&mx[d], (unsigned long long)__double_as_longlong(l[d]),
+                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    pencil_sync<N>();
+#pragma unroll
+    for (int d = 0; d < 3; ++d)
+      lam += tab[TAB_JAC + d] * __longlong_as_double((long long)mx[d]);
+  }
+  return lam;
+}
+
 template <int N, int EPI>
 __device__ __forceinline__ void pencil_tile(PencilLds<N>& s, const StageArgs& a, const Geom& g,
                                             int tile) {
   using P = Pencil<N, EPI>;
   using X = PencilPos<N>;
   constexpr int n = P::n, NL = P::NL, NN = P::NN;
-  const int t = P::WAVE ? (int)(threadIdx.x & 63u) : (int)threadIdx.x;
-  // threads beyond the block's lines repeat its last line, lanes beyond the mesh its last element
-  const bool own = P::FULL || t < P::EB * NL;
-  const int tl = own ? t : P::EB * NL - 1;
-  const int le = tl / NL, line = tl - le * NL;
-  const int lb = line / n, la = line - lb * n;   // the line's place in the other two directions
-  const int er = tile * P::EB + le;
-  const bool on = own && er < g.E;
-  const int e = er < g.E ? er : (int)g.E - 1;
+  const PencilPlace<N> w(g, tile);
+  const int t = w.t, la = w.la, lb = w.lb, line = w.line, le = w.le, e = w.e;
+  const bool on = w.on;
   const size_t ENN = (size_t)g.E * NN;
   const ConstTab tab = const_tab(g.tab);
   const double gm1 = g.gamma - 1.0;
-  int ec[3];
-  elem_xyz(g, e, ec);
-  unsigned ho = ((unsigned)e * NN + line * n) * 8u;   // home: the x line (j, k) = (la, lb)
-  const int eb = X::elem(le);
-  const int bx = X::template at<2>(X::template at<1>(eb, la), lb);
-  const int by = X::template at<2>(X::template at<0>(eb, la), lb);
-  const int bz = X::template at<1>(X::template at<0>(eb, la), lb);
+  const int (&ec)[3] = w.ec;
+  unsigned ho = w.ho;
+  const int bx = w.bx, by = w.by, bz = w.bz;
 
   double um[5][n], un[2][5], unb[2][5], f[2][5], acc[n][5], be[n];
   PLine<n> q;
@@ -535,11 +598,13 @@ __device__ __forceinline__ void pencil_tile(PencilLds<N>& s, const StageArgs& a,
           for (int i = 0; i < n; ++i) st(a.k + v * ENN, ho, i, kv[v][i]);
         }
 #pragma unroll
-        for (int i = 0; i < n; ++i) {
-          um[v][i] = fma(a.B, kv[v][i], um[v][i]);
-          st(a.uout + v * ENN, ho, i, um[v][i]);
-        }
+        for (int i = 0; i < n; ++i) um[v][i] = fma(a.B, kv[v][i], um[v][i]);
       }
+      // (N = 6 and 7 gain nothing from streaming: 24^3 1 271 / 1 270 and 1 665 / 1 722)
+      store_out<5>(N <= 5 ? a.nt_out : 0, [&](int v, auto nt) {
+#pragma unroll
+        for (int i = 0; i < n; ++i) st_out(a.uout + v * ENN, ho, i, um[v][i], nt);
+      });
     }
     phase_fence();
     if (a.speed != nullptr || a.speed_slots != nullptr) {
@@ -548,38 +613,17 @@ __device__ __forceinline__ void pencil_tile(PencilLds<N>& s, const StageArgs& a,
 #pragma unroll
       for (int i = 0; i < n; ++i) {
         const double u5[5] = {um[0][i], um[1][i], um[2][i], um[3][i], um[4][i]};
-        Prim<double> w;
-        ok &= cons_to_prim<3, false>(u5, g.gamma, w);
+        Prim<double> pn;
+        ok &= cons_to_prim<3, false>(u5, g.gamma, pn);
 #pragma unroll
-        for (int d = 0; d < 3; ++d) l[d] = fmax(l[d], fabs(w.v[d]) + w.c);
+        for (int d = 0; d < 3; ++d) l[d] = fmax(l[d], fabs(pn.v[d]) + pn.c);
       }
       if (on && !ok) *g.flag = 1;
-      double lam = 0.0;   // the element's wave speed, in the thread that writes it
-      if constexpr (NL == 16) {
-#pragma unroll
-        for (int d = 0; d < 3; ++d) lam += tab[TAB_JAC + d] * row_max16(l[d]);
-      } else if constexpr (NL == 64) {
-#pragma unroll
-        for (int d = 0; d < 3; ++d) lam += tab[TAB_JAC + d] * wave_max_lane63(l[d]);
-      } else {   // maxima of non-negative doubles as integers, in the buffer
-        unsigned long long* const mx = reinterpret_cast<unsigned long long*>(&s.q[0][0]);
-        pencil_sync<N>();
-        if (line < 3) mx[le * 3 + line] = 0;
-        pencil_sync<N>();
-#pragma unroll
-        for (int d = 0; d < 3; ++d)
-          if (on && l[d] > 0.0)
-            __hip_atomic_fetch_max(&mx[le * 3 + d], (unsigned long long)__double_as_longlong(l[d]),
-                                   __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-        pencil_sync<N>();
-#pragma unroll
-        for (int d = 0; d < 3; ++d)
-          lam += tab[TAB_JAC + d] * __longlong_as_double((long long)mx[le * 3 + d]);
-      }
+      const double lam = pencil_elem_speed<N>(&s.q[0][0], tab, w, l);
       if (a.speed_slots) {
         if constexpr (NL == 16) {   // one atomic per wave
-          const double w = wave_max_lane63(on ? lam : 0.0);
-          if (t == 63) slot_max(a.speed_slots, tile, w);
+          const double mw = wave_max_lane63(on ? lam : 0.0);
+          if (t == 63) slot_max(a.speed_slots, tile, mw);
         } else if (on && line == (NL == 64 ? 63 : 0)) {
           slot_max(a.speed_slots, e, lam);
         }
