@@ -598,13 +598,17 @@ __device__ __forceinline__ void pencil_tile(PencilLds<N>& s, const StageArgs& a,
           for (int i = 0; i < n; ++i) st(a.k + v * ENN, ho, i, kv[v][i]);
         }
 #pragma unroll
-        for (int i = 0; i < n; ++i) um[v][i] = fma(a.B, kv[v][i], um[v][i]);
+        for (int i = 0; i < n; ++i) {
+          um[v][i] = fma(a.B, kv[v][i], um[v][i]);
+          if constexpr (N > 5) st(a.uout + v * ENN, ho, i, um[v][i]);
+        }
       }
       // (N = 6 and 7 gain nothing from streaming: 24^3 1 271 / 1 270 and 1 665 / 1 722)
-      store_out<5>(N <= 5 ? a.nt_out : 0, [&](int v, auto nt) {
+      if constexpr (N <= 5)
+        store_out<5>(a.nt_out, [&](int v, auto nt) {
 #pragma unroll
-        for (int i = 0; i < n; ++i) st_out(a.uout + v * ENN, ho, i, um[v][i], nt);
-      });
+          for (int i = 0; i < n; ++i) st_out(a.uout + v * ENN, ho, i, um[v][i], nt);
+        });
     }
     phase_fence();
     if (a.speed != nullptr || a.speed_slots != nullptr) {

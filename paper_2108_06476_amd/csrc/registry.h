@@ -7,6 +7,7 @@
 #include "curv.h"
 #include "mhd.h"
 #include "pencil.h"
+#include "pencil_mhd.h"
 #include <limits>
 
 namespace dgx {
@@ -78,6 +79,24 @@ struct Launch {
     hipLaunchKernelGGL((k_pencil<N, EPI, WPB>), dim3((unsigned)((g.E + per - 1) / per)),
                        dim3(Pencil<N, EPI>::THREADS * WPB), 0, st, a, g);
     return hipGetLastError();
+  }
+
+  // launched: false below the kernel's smallest mesh (mhd_pencil_min) or without a kernel
+  template <int VOL, int EPI>
+  static bool pencil_mhd1(hipStream_t st, const StageArgs& a, const Geom& g) {
+    constexpr int64_t min_e = mhd_pencil_min<N, VOL, EPI>();
+    if constexpr (min_e < 0) return false;
+    else {
+      if (g.E < min_e || a.surf == SURF_NONE) return false;
+      constexpr int per = PencilMap<N>::EB;   // elements per block
+      hipLaunchKernelGGL((k_pencil_mhd<N, VOL, EPI>), dim3((unsigned)((g.E + per - 1) / per)),
+                         dim3(PencilMap<N>::THREADS), 0, st, a, g);
+      return true;
+    }
+  }
+  template <int VOL>
+  static bool pencil_mhd(hipStream_t st, const StageArgs& a, const Geom& g, int epi) {
+    return epi == EPI_RK ? pencil_mhd1<VOL, EPI_RK>(st, a, g) : pencil_mhd1<VOL, EPI_RHS>(st, a, g);
   }
 
   template <int EPI>
@@ -208,6 +227,9 @@ struct Launch {
           return hipGetLastError();
         }
       }
+      if (vol == VOL_WEAK ? pencil_mhd<VOL_WEAK>(st, a, g, epi)
+                          : vol == VOL_EC && pencil_mhd<VOL_EC>(st, a, g, epi))
+        return hipGetLastError();
       const dim3 grid(blocks(g.E)), block(S::THREADS);
       if (vol == VOL_EC) {
         if (epi == EPI_RK) hipLaunchKernelGGL((k_stage_mhd_ec<N, EPI_RK>), grid, block, 0, st, a, g);
