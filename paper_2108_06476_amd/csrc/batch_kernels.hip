@@ -129,7 +129,7 @@ void k_batch_pencil(BatchLaunch b, int cur, double A, double B, int emit, int kw
   const int item = (int)xcd_tile(blockIdx.x, gridDim.x);
   const int ri = find_run(b, item);
   const RunDesc& d = b.runs[b.order[ri]];
-  pencil_tile<N, EPI>(s, run_args(d, cur, A, B, emit, kw), run_geom(d), item - b.prefix[ri]);
+  pencil_tile<N, EPI, false>(s, run_args(d, cur, A, B, emit, kw), run_geom(d), item - b.prefix[ri]);
 }
 
 // Per element of one tile: sum_d (2/h_d) max over the nodes of |v_d| + c -> speed[e].

@@ -807,6 +807,51 @@ __device__ __forceinline__ double stage_epilogue(unsigned char* xb, const StageA
   return dt_used;
 }
 
+// The raw blending factor from the modal energies of all modes and of the index cubes
+// [0, N-1]^d and [0, N-2]^d; en: the ratio it is formed from.
+__device__ __forceinline__ double indicator_alpha(double t0, double t1, double t2, double thr,
+                                                  double sharp, double alpha_min,
+                                                  double alpha_max, double xcut, double& en) {
+  // the ratios and the logistic with refined hardware reciprocals (full float64 accuracy)
+  const double r1 = t0 != 0.0 ? (t0 - t1) * rcp_nr(t0) : 0.0;
+  const double r2 = t1 != 0.0 ? (t1 - t2) * rcp_nr(t1) : 0.0;
+  en = fmax(r1, r2);
+  // the logistic 1/(1 + exp(-x)) lies below alpha_min for x < -xcut and above
+  // 1 - alpha_min for x > xcut (xcut = ln(1/alpha_min - 1)); beyond those by a margin the
+  // clipped value is known without the exponential
+  const double x = sharp * (en - thr);
+  double al;
+  if (x < -xcut - 1e-3) {
+    al = 0.0;
+  } else if (x > xcut + 1e-3) {
+    al = 1.0;
+  } else {
+    al = rcp_nr(1.0 + exp(-x));
+    if (al < alpha_min) al = 0.0;
+    else if (al > 1.0 - alpha_min) al = 1.0;
+  }
+  return fmin(al, alpha_max);
+}
+
+// Shock capturing: an element's blending factor, its own or half a face neighbour's raw
+// indicator, whichever is larger (or the given field).
+template <int DIM>
+__device__ __forceinline__ double blending_factor(const StageArgs& a, const Geom& g, int e) {
+  if (!a.alpha_raw_in) return a.alpha[e];
+  const double* ar = a.alpha_raw_in;
+  double v = ar[e];
+  if (a.alpha_smooth) {
+    int ec[3];
+    elem_xyz(g, e, ec);
+#pragma unroll
+    for (int d = 0; d < DIM; ++d) {
+      v = fmax(v, 0.5 * ar[elem_nb(g, e, ec, d, -1)]);
+      v = fmax(v, 0.5 * ar[elem_nb(g, e, ec, d, 1)]);
+    }
+  }
+  return v;
+}
+
 // The indicator of one element from q = rho p at its nodes: w0, w1, w2 are NN-double LDS
 // scratch arrays of the element (w0 holds q on entry), sV the LDS V^-1 table.  Called by
 // every thread of the block (inb: the thread has an element slot; active: its element
@@ -881,26 +926,8 @@ __device__ __forceinline__ void indicator_elem(double* w0, double* w1, double* w
     t2 = w2[0];
   }
   if (active && node == last) {
-    // the ratios and the logistic with refined hardware reciprocals (full float64 accuracy)
-    const double r1 = t0 != 0.0 ? (t0 - t1) * rcp_nr(t0) : 0.0;
-    const double r2 = t1 != 0.0 ? (t1 - t2) * rcp_nr(t1) : 0.0;
-    const double en = fmax(r1, r2);
-    // the logistic 1/(1 + exp(-x)) lies below alpha_min for x < -xcut and above
-    // 1 - alpha_min for x > xcut (xcut = ln(1/alpha_min - 1)); beyond those by a margin the
-    // clipped value is known without the exponential
-    const double x = sharp * (en - thr);
-    double al;
-    if (x < -xcut - 1e-3) {
-      al = 0.0;
-    } else if (x > xcut + 1e-3) {
-      al = 1.0;
-    } else {
-      al = rcp_nr(1.0 + exp(-x));
-      if (al < alpha_min) al = 0.0;
-      else if (al > 1.0 - alpha_min) al = 1.0;
-    }
-    al = fmin(al, alpha_max);
-    alpha_raw[e] = al;
+    double en;
+    alpha_raw[e] = indicator_alpha(t0, t1, t2, thr, sharp, alpha_min, alpha_max, xcut, en);
     if (energy) energy[e] = en;
   }
 }
@@ -937,24 +964,7 @@ __device__ __forceinline__ void stage_tile(typename StageLdsOf<DIM, N, VOL, RT, 
   if (active) {
 #pragma unroll
     for (int v = 0; v < NV; ++v) um[v] = (a.uin + (size_t)e * NN + (size_t)v * ENN)[(unsigned)node];
-    if constexpr (VOL == VOL_SHOCKCAP) {
-      if (a.alpha_raw_in) {   // alpha_e = max(raw_e, raw of the face neighbours / 2)
-        const double* ar = a.alpha_raw_in;
-        double v = ar[e];
-        if (a.alpha_smooth) {
-          int ec[3];
-          elem_xyz(g, e, ec);
-#pragma unroll
-          for (int d = 0; d < DIM; ++d) {
-            v = fmax(v, 0.5 * ar[elem_nb(g, e, ec, d, -1)]);
-            v = fmax(v, 0.5 * ar[elem_nb(g, e, ec, d, 1)]);
-          }
-        }
-        al_e = v;
-      } else {
-        al_e = a.alpha[e];
-      }
-    }
+    if constexpr (VOL == VOL_SHOCKCAP) al_e = blending_factor<DIM>(a, g, e);
     if constexpr (sizeof(RT) == 4 && !WaveElem<DIM, N>::value) {
       double u0[NV];
 #pragma unroll

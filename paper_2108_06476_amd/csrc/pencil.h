@@ -141,13 +141,13 @@ __device__ __forceinline__ void st(double* base, unsigned off, int i, double v) 
   reinterpret_cast<double*>(reinterpret_cast<char*>(base) + off)[i] = v;
 }
 
-// A line's nodes: density, velocity (v[0] along the line, then the other two in cyclic order),
-// twice the pressure and the energy.
 template <typename NT>
 __device__ __forceinline__ void st_out(double* base, unsigned off, int i, double v, NT nt) {
   store_one(reinterpret_cast<double*>(reinterpret_cast<char*>(base) + off) + i, v, nt);
 }
 
+// A line's nodes: density, velocity (v[0] along the line, then the other two in cyclic order),
+// twice the pressure and the energy.
 template <int n>
 struct PLine {
   double rho[n], v[3][n], p2[n], E[n];
@@ -231,10 +231,11 @@ __device__ __forceinline__ void pencil_far(double a, double b, double c, double 
 // Two-point fluxes of every pair of the line, contracted into acc (scaled as pencil_pair's).
 // be: (gamma - 1) beta / 2 of the nodes.  The near-equal series serves all lanes; where a lane
 // of the wave is beyond it, the row's means are formed again one pair at a time, in a loop
-// that keeps the code and the registers of that rare path small.
-template <int n, int ROW, typename Park, typename Unpark>
-__device__ __forceinline__ void pencil_volume(PLine<n>& q, double (&be)[n], ConstTab S, Park park,
-                                              Unpark unpark, double (&acc)[n][5]) {
+// that keeps the code and the registers of that rare path small.  SC: every contribution times
+// dg (the share of the flux differencing where it is blended).
+template <int n, int ROW, bool SC, typename Park, typename Unpark>
+__device__ __forceinline__ void pencil_volume(PLine<n>& q, double (&be)[n], ConstTab S, double dg,
+                                              Park park, Unpark unpark, double (&acc)[n][5]) {
   const double c1 = sconst(-1.0 / 6.0), c2 = sconst(-2.0 / 45.0), c3 = -22.0 / 945.0;
   const double e1 = sconst(2.0 / 3.0), e2 = sconst(2.0 / 5.0), e3 = 2.0 / 7.0;
 #pragma unroll
@@ -282,7 +283,11 @@ __device__ __forceinline__ void pencil_volume(PLine<n>& q, double (&be)[n], Cons
         double f[5];
         pencil_pair(rl[m - m0], ib[m - m0], q.v[0][i], q.v[1][i], q.v[2][i], q.p2[i], q.v[0][m],
                     q.v[1][m], q.v[2][m], q.p2[m], f);
-        const double cim = S[i * TMAX + m], cmi = S[m * TMAX + i];
+        double cim = S[i * TMAX + m], cmi = S[m * TMAX + i];
+        if constexpr (SC) {
+          cim *= dg;
+          cmi *= dg;
+        }
 #pragma unroll
         for (int v = 0; v < 5; ++v) {
           acc[i][v] = fma(cim, f[v], acc[i][v]);
@@ -415,6 +420,120 @@ __device__ __forceinline__ void pencil_faces(const Geom& g, int surf, ConstTab t
               tab[TAB_LIFT + 2 * D + 1], f[1]);
 }
 
+// The line as conserved states with their primitives, node m.
+template <int n>
+__device__ __forceinline__ void pencil_node(const PLine<n>& q, int m, double gamma, double (&u)[5],
+                                            Prim<double>& p) {
+  p.rho = q.rho[m];
+  p.p = 0.5 * q.p2[m];
+  p.c = sqrt_pos1(gamma * p.p * rcp_nr1(p.rho));
+  u[0] = p.rho;
+  u[4] = q.E[m];
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    p.v[k] = q.v[k][m];
+    u[1 + k] = p.rho * p.v[k];
+  }
+}
+
+// Subcell finite-volume part of a line (fv_dir), weighted by al and scaled as pencil_pair's:
+// w: -(2/h)/w_i of the direction.
+template <int n>
+__device__ __forceinline__ void pencil_fv(const PLine<n>& q, int fvf, double gamma, ConstTab w,
+                                          double al, double (&acc)[n][5]) {
+  double uL[5], uR[5];
+  Prim<double> L, R;
+  pencil_node<n>(q, 0, gamma, uL, L);
+#pragma unroll
+  for (int m = 0; m < n - 1; ++m) {
+    pencil_node<n>(q, m + 1, gamma, uR, R);
+    double F[5];
+    const double h = fvf == SURF_LLF ? llf_flux<3, 0>(uL, L, uR, R, gamma, F)
+                                     : hll_flux<3, 0>(uL, L, uR, R, gamma, F);
+    const double ah = 4.0 * al * h, a = ah * w[m], b = ah * w[m + 1];
+    acc[m][0] = fma(0.5 * a, F[0], acc[m][0]);
+    acc[m + 1][0] = fma(-0.5 * b, F[0], acc[m + 1][0]);
+#pragma unroll
+    for (int v = 1; v < 5; ++v) {
+      acc[m][v] = fma(a, F[v], acc[m][v]);
+      acc[m + 1][v] = fma(-b, F[v], acc[m + 1][v]);
+    }
+#pragma unroll
+    for (int v = 0; v < 5; ++v) {
+      asm("" : "+v"(acc[m][v]), "+v"(acc[m + 1][v]));
+      uL[v] = uR[v];
+    }
+    L = R;
+  }
+}
+
+// Sum over each row of 16 lanes, in every lane of the row.
+__device__ __forceinline__ double row_sum16(double x) {
+  x += dpp_f64<0xB1, 0xF>(0.0, x);
+  x += dpp_f64<0x4E, 0xF>(0.0, x);
+  x += dpp_f64<0x141, 0xF>(0.0, x);
+  return x + dpp_f64<0x140, 0xF>(0.0, x);
+}
+
+// The raw indicator of the home lines' new state (k_indicator's computation): the transform of
+// rho p line by line in x, y and z through a plane of the buffer, the energies summed over the
+// element's sixteen lanes.
+template <int N>
+__device__ __forceinline__ void pencil_indicator(double* buf, const StageArgs& a, const Geom& g,
+                                                 const PencilPlace<N>& w, ConstTab V,
+                                                 const double (&um)[5][N + 1]) {
+  using X = PencilPos<N>;
+  constexpr int n = N + 1;
+  static_assert(PencilMap<N>::NL == 16, "an element is a row of lanes");
+  double in[n], out[n];
+  bool ok = true;
+#pragma unroll
+  for (int i = 0; i < n; ++i) {
+    const double u5[5] = {um[0][i], um[1][i], um[2][i], um[3][i], um[4][i]};
+    ok &= rho_p<3>(u5, g.gamma, in[i]);
+  }
+  if (w.on && !ok) *g.flag = 1;
+  auto transform = [&]() {
+#pragma unroll
+    for (int i = 0; i < n; ++i) {
+      out[i] = 0.0;
+#pragma unroll
+      for (int m = 0; m < n; ++m) out[i] = fma(V[i * TMAX + m], in[m], out[i]);
+    }
+  };
+  transform();
+  pencil_sync<N>();
+#pragma unroll
+  for (int i = 0; i < n; ++i) buf[X::template at<0>(w.bx, i)] = out[i];
+  pencil_sync<N>();
+#pragma unroll
+  for (int i = 0; i < n; ++i) in[i] = buf[X::template at<1>(w.by, i)];
+  transform();
+#pragma unroll
+  for (int i = 0; i < n; ++i) buf[X::template at<1>(w.by, i)] = out[i];
+  pencil_sync<N>();
+#pragma unroll
+  for (int i = 0; i < n; ++i) in[i] = buf[X::template at<2>(w.bz, i)];
+  transform();
+  double t0 = 0.0, t1 = 0.0, t2 = 0.0;
+#pragma unroll
+  for (int i = 0; i < n; ++i) {
+    const double c = out[i] * out[i];
+    const int mx = max(i, max(w.la, w.lb));
+    t0 += c;
+    t1 += mx <= N - 1 ? c : 0.0;
+    t2 += mx <= N - 2 ? c : 0.0;
+  }
+  t0 = row_sum16(t0);
+  t1 = row_sum16(t1);
+  t2 = row_sum16(t2);
+  if (w.on && w.line == 0) {
+    double en;
+    a.alpha_next[w.e] = indicator_alpha(t0, t1, t2, a.ind_thr, a.ind_sharp, a.ind_amin,
+                                        a.ind_amax, a.ind_xcut, en);
+  }
+}
+
 // Max over each row of 16 lanes, in every lane of the row (see wave_max_lane63).
 __device__ __forceinline__ double row_max16(double x) {
   x = fmax(x, dpp_f64<0xB1, 0xF>(x, x));
@@ -455,7 +574,9 @@ __device__ __forceinline__ double pencil_elem_speed(double* buf, ConstTab tab,
   return lam;
 }
 
-template <int N, int EPI>
+// SC: the volume blended with the subcell finite volumes by the element's factor, and the
+// indicator of the output state (N = 3).
+template <int N, int EPI, bool SC>
 __device__ __forceinline__ void pencil_tile(PencilLds<N>& s, const StageArgs& a, const Geom& g,
                                             int tile) {
   using P = Pencil<N, EPI>;
@@ -473,6 +594,18 @@ __device__ __forceinline__ void pencil_tile(PencilLds<N>& s, const StageArgs& a,
 
   double um[5][n], un[2][5], unb[2][5], f[2][5], acc[n][5], be[n];
   PLine<n> q;
+  double al = 0.0, dg = 1.0;
+  if constexpr (SC) {
+    al = blending_factor<3>(a, g, e);
+    dg = 1.0 - al;
+  }
+  // the subcell part of the line's direction d, where the element blends
+  auto subcell = [&](int d) {
+    if constexpr (SC) {
+      if (al != 0.0) pencil_fv<n>(q, a.fvf, g.gamma, tab + TAB_FV + d * TMAX, al, acc);
+      phase_fence();
+    }
+  };
   auto load_u = [&]() {
 #pragma unroll
     for (int v = 0; v < 5; ++v)
@@ -518,7 +651,8 @@ __device__ __forceinline__ void pencil_tile(PencilLds<N>& s, const StageArgs& a,
   phase_fence();
   if constexpr (P::PRE) pencil_face_load<N, 0>(a.uin, g, e, ec, la, lb, ENN, un);
   phase_fence();
-  pencil_volume<n, P::ROW>(q, be, tab + TAB_S + 2 * TMAX * TMAX, []() {}, []() {}, acc);
+  subcell(2);
+  pencil_volume<n, P::ROW, SC>(q, be, tab + TAB_S + 2 * TMAX * TMAX, dg, []() {}, []() {}, acc);
   phase_fence();
 
   // ---- y: once its lines are in registers the buffer takes the sums
@@ -536,9 +670,10 @@ __device__ __forceinline__ void pencil_tile(PencilLds<N>& s, const StageArgs& a,
     acc[N][v] += f[1][v];
   }
   // (a far row's sums wait at their places in the buffer)
-  pencil_volume<n, P::ROW>(q, be, tab + TAB_S + 1 * TMAX * TMAX,
-                   [&]() { pencil_sums_put<N, 1>(s, by, acc); },
-                   [&]() { pencil_sums_get<N, 1>(s, by, acc); }, acc);
+  subcell(1);
+  pencil_volume<n, P::ROW, SC>(q, be, tab + TAB_S + 1 * TMAX * TMAX, dg,
+                               [&]() { pencil_sums_put<N, 1>(s, by, acc); },
+                               [&]() { pencil_sums_get<N, 1>(s, by, acc); }, acc);
   phase_fence();
   if constexpr (!P::HOLD) load_u();
   if constexpr (!P::PRE) pencil_face_load<N, 0>(a.uin, g, e, ec, la, lb, ENN, un);
@@ -564,8 +699,10 @@ __device__ __forceinline__ void pencil_tile(PencilLds<N>& s, const StageArgs& a,
     acc[0][v] += f[0][v];
     acc[N][v] += f[1][v];
   }
-  pencil_volume<n, P::ROW>(q, be, tab + TAB_S, [&]() { pencil_sums_put<N, 0>(s, bx, acc); },
-                   [&]() { pencil_sums_get<N, 0>(s, bx, acc); }, acc);
+  subcell(0);
+  pencil_volume<n, P::ROW, SC>(q, be, tab + TAB_S, dg,
+                               [&]() { pencil_sums_put<N, 0>(s, bx, acc); },
+                               [&]() { pencil_sums_get<N, 0>(s, bx, acc); }, acc);
   phase_fence();
 
   // epilogue: acc[i][v] holds twice (v = 0) and four times the home line's right-hand side
@@ -635,6 +772,9 @@ __device__ __forceinline__ void pencil_tile(PencilLds<N>& s, const StageArgs& a,
         a.speed[e] = lam;
       }
     }
+    if constexpr (SC) {
+      if (a.alpha_next) pencil_indicator<N>(&s.q[0][0], a, g, w, tab + TAB_VINV, um);
+    }
     if (a.t_step && blockIdx.x == 0 && threadIdx.x == 0) stage_time_publish(a, dt);
     if (a.slots_clear && blockIdx.x == 0 && threadIdx.x < (unsigned)DT_SLOTS)
       a.slots_clear[threadIdx.x * DT_SLOT_STRIDE] = 0.0;
@@ -656,12 +796,22 @@ inline bool use_pencil(int N, int64_t E, int surf) {
   const int64_t nn = (int64_t)(N + 1) * (N + 1) * (N + 1);
   return E >= min_E[N - 3] && E * nn <= ((int64_t)1 << 28);
 }
+// The same with shock capturing (N = 3; single-wave blocks: 64^3 3 590 us per step, 3 630 with
+// two waves, 3 700 with four).  Sedov blast, microseconds per step: 16^3 109 / 122, 20^3 168 / 166,
+// 24^3 282 / 284, 27^3 398 / 358, 32^3 608 / 520, 48^3 1 717 / 1 550, 64^3 4 045 / 3 590; right-hand
+// side 24^3 54.5 / 54.3, 64^3 664 / 616.  A stage at 32^3 moves 336 MB in 93 us (3.6 TB/s), N = 3
+// without blending the same in 65: what bounds it beyond memory are the waves of blending
+// elements, whose lines form three subcell fluxes more in each direction, and the indicator's
+// three passes through the LDS.
+inline bool use_pencil_shock(int64_t E, int surf) {
+  return E >= 16384 && E <= ((int64_t)1 << 22) && (surf == SURF_LLF || surf == SURF_HLL);
+}
 // Four waves per block (x neighbours share an L1: N = 3, 64^3 3 040 us per step, against 3 240
 // with one) from here on; below, single-wave blocks even out the last round (32^3: 342 / 358).
 constexpr int64_t PENCIL_WIDE_E = 40960;
 
 // WPB: independent waves per block where a wave holds its elements whole, else 1.
-template <int N, int EPI, int WPB>
+template <int N, int EPI, int WPB, bool SC = false>
 __global__ __launch_bounds__((Pencil<N, EPI>::THREADS * WPB))
 __attribute__((amdgpu_waves_per_eu((Pencil<N, EPI>::WAVES), (Pencil<N, EPI>::WAVES))))
 void k_pencil(StageArgs a, Geom g) {
@@ -670,7 +820,7 @@ void k_pencil(StageArgs a, Geom g) {
   const int w = P::WAVE ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) : 0;
   const int tile = (int)xcd_tile(blockIdx.x, gridDim.x) * WPB + w;
   if ((int64_t)tile * P::EB >= g.E) return;   // (whole waves; the last block starts inside)
-  pencil_tile<N, EPI>(s[w], a, g, tile);
+  pencil_tile<N, EPI, SC>(s[w], a, g, tile);
 }
 
 }  // namespace dgx

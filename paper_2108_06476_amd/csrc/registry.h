@@ -73,10 +73,10 @@ struct Launch {
     return hipGetLastError();
   }
 
-  template <int EPI, int WPB>
+  template <int EPI, int WPB, bool SC = false>
   static hipError_t pencil1(hipStream_t st, const StageArgs& a, const Geom& g) {
     constexpr int per = Pencil<N, EPI>::EB * WPB;   // elements per block
-    hipLaunchKernelGGL((k_pencil<N, EPI, WPB>), dim3((unsigned)((g.E + per - 1) / per)),
+    hipLaunchKernelGGL((k_pencil<N, EPI, WPB, SC>), dim3((unsigned)((g.E + per - 1) / per)),
                        dim3(Pencil<N, EPI>::THREADS * WPB), 0, st, a, g);
     return hipGetLastError();
   }
@@ -116,7 +116,12 @@ struct Launch {
     if (prec != PREC_FP64) return hipErrorInvalidValue;
     if (vol == VOL_CENTRAL) return stage1<VOL_CENTRAL, EPI, double>(st, a, g);
     if (vol == VOL_NONE) return stage1<VOL_NONE, EPI, double>(st, a, g);
-    if (vol == VOL_SHOCKCAP) return stage1<VOL_SHOCKCAP, EPI, double>(st, a, g);
+    if (vol == VOL_SHOCKCAP) {
+      if constexpr (DIM == 3 && N == 3) {
+        if (use_pencil_shock(g.E, a.surf)) return pencil1<EPI, 1, true>(st, a, g);
+      }
+      return stage1<VOL_SHOCKCAP, EPI, double>(st, a, g);
+    }
     if (vol == VOL_WEAK) return stage1<VOL_WEAK, EPI, double>(st, a, g);
     if (vol == VOL_WEAK_MFMA) {
       if constexpr (DIM == 3 && N == 3) return stage1<VOL_WEAK_MFMA, EPI, double>(st, a, g);
