@@ -245,12 +245,14 @@ typedef struct dgx_batch_s *dgx_batch;
 
 /* nruns configurations (host array, copied); every run is 3D, DGX_VOL_EC, DGX_SURF_LLF or
  * HLL, polydeg 3..5, with its own grid, extent and gamma; all share one precision (the
- * many independent instances of Section 2.3.3).  Each RK stage of all runs is one launch
- * over (run, element tile) work items, runs of higher polydeg first.  The launch takes one
+ * many independent instances of Section 2.3.3).  An RK stage of all runs is one launch
+ * over (run, element tile) work items, runs of higher polydeg first, and one launch per
+ * polydeg over the runs large enough for a line of nodes per thread.  The former takes one
  * block per work item unless the tuner (or dgx_batch_set_shape) picks a persistent grid
  * whose blocks loop over the items; one block per item is the default and what the tuner
  * normally keeps, since the persistent loop holds more registers live.  A step (per-run
- * dt + 5 stages) is replayed from a captured hipGraph.  The library owns each run's second
+ * dt + 5 stages) is replayed from a captured hipGraph, a branch for each of these launches'
+ * runs.  The library owns each run's second
  * state buffer and RK register (they are not passed in: a stage reads its input buffer's
  * face neighbours while it writes the other). */
 dgx_status dgx_batch_create(const dgx_config *cfgs, int32_t nruns, void *hip_stream,

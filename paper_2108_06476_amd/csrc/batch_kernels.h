@@ -1,5 +1,6 @@
 // batch_kernels.h -- ensembles of independent 3D runs (uneven grids, polydeg 3..5)
-// advanced by one launch per RK stage over the element tiles of all runs.
+// advanced by one launch per RK stage over the element tiles of all runs, and one per degree for
+// the runs with a line of nodes per thread.
 #pragma once
 #include <hip/hip_runtime.h>
 

@@ -103,3 +103,22 @@ def test_batch_equals_single_runs(runs):
             s.step(u, steps, cfl=0.5, t=t)
             assert torch.equal(ub[r], u) and float(tb[r]) == float(t[0]), (steps, r)
     assert b.check() == 0
+
+
+def test_batch_branches_replayed():
+    """The steps' graph, whose branches are the groups of runs, replayed with eager work and
+    synchronisations between the replays."""
+    runs = [(4, (24, 23, 23)), (5, (19, 17, 16)), (3, (29, 27, 27)), (3, (8, 7, 9)), (4, (3, 2, 2))]
+    cfgs = [_cfg(N, cells, "llf") for N, cells in runs]
+    singles = [dgx.Solver(**c) for c in cfgs]
+    us = [inputs.tgv(s.node_coords(), perturb_seed=50 + i).contiguous() for i, s in enumerate(singles)]
+    refs = [u.clone() for u in us]
+    b = dgx.Batch(cfgs)
+    for steps in (2, 4, 2, 6):
+        b.step(us, steps, cfl=0.5)
+        for r, s in enumerate(singles):
+            s.step(refs[r], steps, cfl=0.5)
+            assert torch.equal(us[r], refs[r]), (steps, r)
+        us[0].mul_(1.0)
+        torch.cuda.synchronize()
+    assert b.check() == 0
