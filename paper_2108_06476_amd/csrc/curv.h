@@ -419,7 +419,7 @@ __global__ __launch_bounds__(256) void k_stage_curv_split(StageArgs a, Geom g) {
     R[v] = (((s.x[0][v][node] + s.x[1][v][node]) + s.x[2][v][node]) + s.x[3][v][node]) * ij +
            s.src[v][node];
   // wave 0 alone: the epilogue's element-wide reductions are wave reductions
-  stage_epilogue<3, N, 5, EPI, 256>(
+  stage_epilogue<3, N, 5, EPI, 256, false>(
       nullptr, a, g, 0, node, e, true, true, ENN, own_ix, um, R,
       [&](const double (&unew)[5], double (&ls)[3]) {
         Prim<double> q;

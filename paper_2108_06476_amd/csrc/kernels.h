@@ -703,9 +703,10 @@ __device__ __forceinline__ void weak_dir(const L& s, int base, int node, const d
 // xb: the block's per-element LDS slots (elements of several waves reduce through them).
 // DTF: the caller may ask for the first stage's dt to be derived here (a.dt_from) and for
 // the last stage's wave speeds to be folded into slots (a.speed_slots).
-// STREAM: uout may go past the cache (a.nt_out).
-template <int DIM, int N, int NV, int EPI, int BUDGET, typename SpeedFn, bool DTF = false,
-          bool STREAM = true>
+// STREAM: uout may go past the cache (a.nt_out); off in kernels of meshes that fit it, whose short
+// stages the extra branch lengthens (5^3 warped mesh 0.7 %).
+template <int DIM, int N, int NV, int EPI, int BUDGET, bool STREAM = true, bool DTF = false,
+          typename SpeedFn>
 __device__ __forceinline__ double stage_epilogue(unsigned char* xb, const StageArgs& a,
                                                const Geom& g, int le, int node, int e, bool inb,
                                                bool active, size_t ENN, size_t own_ix,
@@ -1121,7 +1122,7 @@ __device__ __forceinline__ void stage_tile(typename StageLdsOf<DIM, N, VOL, RT, 
   // The float64 flux-differencing kernels of N >= 3 serve the meshes below use_pencil's line,
   // which fit the cache; the branch of the streaming store costs them 3 % (8^3 to 10^3).
   constexpr bool STREAM = !(VOL == VOL_EC && sizeof(RT) == 8 && (DIM == 2 || N >= 3));
-  const double dt_used = stage_epilogue<DIM, N, NV, EPI, BUDGET, decltype(speeds), true, STREAM>(
+  const double dt_used = stage_epilogue<DIM, N, NV, EPI, BUDGET, STREAM, true>(
       s.xb, a, g, le, node, e, inb, active, ENN, own_ix, um, R, speeds, IND ? un : nullptr);
   // shock capturing: the raw indicator of the state just written, for the next stage (the
   // computation of k_indicator on the same values, in the element's LDS slot)
