@@ -14,7 +14,7 @@
 // Runge-Kutta stage moves 3.1 GB (counted between the L2s and the rest, 2.4 GB algorithmic) in
 // 600 us, 5.2 TB/s of the 6.0 TB/s that a copy reaches.
 //
-// The lines change threads through LDS (five planes of the block's nodes): first the primitives
+// The lines change threads through LDS (five planes of the block's nodes): first the states
 // of the home lines (x), read in z and y layout; when the y lines are in registers the buffer
 // takes the z sums, then the z and y sums, on their way to the home lines.  The conserved home
 // line stays in registers for the x primitives and the update where they allow it; reading it
@@ -65,7 +65,7 @@ struct Pencil : PencilMap<N> {
 // LDS buffer: [variable][node of the block's (wave's) elements].
 template <int N>
 struct PencilLds {
-  double q[5][PencilMap<N>::EB * PencilMap<N>::NN];   // (rho, v, E); then sums
+  double q[5][PencilMap<N>::EB * PencilMap<N>::NN];   // the conserved state; then sums
 };
 
 // Position in a plane of the buffer of node (i, j, k) of element slot le.  n = 4: i ^ 4j ^ 37k ^
@@ -146,11 +146,13 @@ __device__ __forceinline__ void st_out(double* base, unsigned off, int i, double
   store_one(reinterpret_cast<double*>(reinterpret_cast<char*>(base) + off) + i, v, nt);
 }
 
-// A line's nodes: density, velocity (v[0] along the line, then the other two in cyclic order),
-// twice the pressure and the energy.
+// A line's nodes: density, momentum and velocity (component 0 along the line, then the other two in
+// cyclic order), twice the pressure and the energy.  Interface and subcell fluxes take the momentum
+// as it is stored, as every kernel does: formed again as rho v it would be off by v's rounding
+// (2.3e-15, to one side), and the two elements of a face would see different jumps.
 template <int n>
 struct PLine {
-  double rho[n], v[3][n], p2[n], E[n];
+  double rho[n], m[3][n], v[3][n], p2[n], E[n];
 };
 
 // Twice the pressure from rho, v (components x, y, z: the same value whatever the line's
@@ -305,40 +307,40 @@ __device__ __forceinline__ void pencil_volume(PLine<n>& q, double (&be)[n], Cons
   }
 }
 
-// Lifted interface flux at one end of a line (scaled as pencil_pair's); un: the state across
-// the face.
-__device__ __forceinline__ void pencil_face(const Geom& g, int surf, bool plus, double rho,
-                                            double v0, double v1, double v2, double p2, double E,
-                                            const double (&un)[5], double lift, double (&out)[5]) {
-  Prim<double> qn, qm;
-  if (!cons_to_prim<3, false>(un, g.gamma, qn)) *g.flag = 1;
-  qm.rho = rho;
-  qm.v[0] = v0;
-  qm.v[1] = v1;
-  qm.v[2] = v2;
-  qm.p = 0.5 * p2;
-  double F[5], half;
-  qm.c = sqrt_pos1(g.gamma * qm.p * rcp_nr1(rho));
-  double um[5];
-  um[0] = rho;
-  um[1] = rho * v0;
-  um[2] = rho * v1;
-  um[3] = rho * v2;
-  um[4] = E;   // as loaded: formed from p it would carry a rounding of E into the jump
-  if (surf == SURF_LLF) {
-    double fo[5], fn[5];
-    phys_flux<3, 0>(um, qm, fo);
-    phys_flux<3, 0>(un, qn, fn);
-    const double lam = fmax(fabs(qm.v[0]) + qm.c, fabs(qn.v[0]) + qn.c);
-    const double sl = plus ? lam : -lam;
+// Primitives of a face state: component k of the vectors along direction D + k.  Both sides of an
+// interface form them with the same operations (the kinetic energy in the order x, y, z), so its
+// two elements evaluate the same flux.
+__device__ __forceinline__ void pencil_face_prim(double gamma, double rho, double v0, double v1,
+                                                 double v2, double p2, Prim<double>& q) {
+  q.rho = rho;
+  q.v[0] = v0;
+  q.v[1] = v1;
+  q.v[2] = v2;
+  q.p = 0.5 * p2;
+  q.c = sqrt_pos1(gamma * q.p * rcp_nr1(rho));
+}
+
+// Lifted interface flux at one end of a line (scaled as pencil_pair's), node m; un: the state
+// across the face.
+template <int D, int n>
+__device__ __forceinline__ void pencil_face(const Geom& g, int surf, bool plus, const PLine<n>& q,
+                                            int m, const double (&un)[5], double lift,
+                                            double (&out)[5]) {
+  const double um[5] = {q.rho[m], q.m[0][m], q.m[1][m], q.m[2][m], q.E[m]};
+  Prim<double> qm, qn;
+  pencil_face_prim(g.gamma, um[0], q.v[0][m], q.v[1][m], q.v[2][m], q.p2[m], qm);
+  const double inv = rcp_nr1(un[0]);
+  double vn[3];
 #pragma unroll
-    for (int v = 0; v < 5; ++v) F[v] = (fo[v] + fn[v]) - sl * (un[v] - um[v]);
-    half = 0.5;
-  } else if (plus) {
-    half = hll_flux<3, 0>(um, qm, un, qn, g.gamma, F);
-  } else {
-    half = hll_flux<3, 0>(un, qn, um, qm, g.gamma, F);
-  }
+  for (int k = 0; k < 3; ++k) vn[k] = un[1 + k] * inv;
+  const double p2 = pencil_p2(g.gamma - 1.0, un[0], vn[(3 - D) % 3], vn[(4 - D) % 3], vn[(5 - D) % 3], un[4]);
+  pencil_face_prim(g.gamma, un[0], vn[0], vn[1], vn[2], p2, qn);
+  if (!((un[0] > 0.0) && (p2 > 0.0) && (p2 < 2.0e300) && (un[0] < 1.0e300))) *g.flag = 1;
+  double F[5], half;
+  if (surf == SURF_LLF)
+    half = plus ? llf_flux<3, 0>(um, qm, un, qn, g.gamma, F) : llf_flux<3, 0>(un, qn, um, qm, g.gamma, F);
+  else
+    half = plus ? hll_flux<3, 0>(um, qm, un, qn, g.gamma, F) : hll_flux<3, 0>(un, qn, um, qm, g.gamma, F);
   const double c = half * lift;
   out[0] = 2.0 * c * F[0];
 #pragma unroll
@@ -365,7 +367,7 @@ __device__ __forceinline__ void pencil_face_load(const double* __restrict__ u, c
   }
 }
 
-// A line's primitives from the LDS.
+// A line's states and primitives from the LDS.
 template <int N, int D>
 __device__ __forceinline__ void pencil_read(const PencilLds<N>& s, int bl, double gm1,
                                             PLine<N + 1>& q, double (&be)[N + 1]) {
@@ -373,8 +375,12 @@ __device__ __forceinline__ void pencil_read(const PencilLds<N>& s, int bl, doubl
   for (int m = 0; m < N + 1; ++m) {
     const int x = PencilPos<N>::template at<D>(bl, m);
     q.rho[m] = s.q[0][x];
+    const double inv = rcp_nr1(q.rho[m]);
 #pragma unroll
-    for (int k = 0; k < 3; ++k) q.v[k][m] = s.q[1 + (D + k) % 3][x];
+    for (int k = 0; k < 3; ++k) {
+      q.m[k][m] = s.q[1 + (D + k) % 3][x];
+      q.v[k][m] = q.m[k][m] * inv;
+    }
     q.E[m] = s.q[4][x];
     q.p2[m] = pencil_p2(gm1, q.rho[m], q.v[(3 - D) % 3][m], q.v[(4 - D) % 3][m],
                         q.v[(5 - D) % 3][m], q.E[m]);
@@ -414,10 +420,8 @@ template <int N, int D>
 __device__ __forceinline__ void pencil_faces(const Geom& g, int surf, ConstTab tab,
                                              const PLine<N + 1>& q, const double (&un)[2][5],
                                              double (&f)[2][5]) {
-  pencil_face(g, surf, false, q.rho[0], q.v[0][0], q.v[1][0], q.v[2][0], q.p2[0], q.E[0], un[0],
-              tab[TAB_LIFT + 2 * D], f[0]);
-  pencil_face(g, surf, true, q.rho[N], q.v[0][N], q.v[1][N], q.v[2][N], q.p2[N], q.E[N], un[1],
-              tab[TAB_LIFT + 2 * D + 1], f[1]);
+  pencil_face<D, N + 1>(g, surf, false, q, 0, un[0], tab[TAB_LIFT + 2 * D], f[0]);
+  pencil_face<D, N + 1>(g, surf, true, q, N, un[1], tab[TAB_LIFT + 2 * D + 1], f[1]);
 }
 
 // The line as conserved states with their primitives, node m.
@@ -432,7 +436,7 @@ __device__ __forceinline__ void pencil_node(const PLine<n>& q, int m, double gam
 #pragma unroll
   for (int k = 0; k < 3; ++k) {
     p.v[k] = q.v[k][m];
-    u[1 + k] = p.rho * p.v[k];
+    u[1 + k] = q.m[k][m];
   }
 }
 
@@ -620,7 +624,10 @@ __device__ __forceinline__ void pencil_tile(PencilLds<N>& s, const StageArgs& a,
       const double inv = rcp_nr1(um[0][i]);
       q.rho[i] = um[0][i];
 #pragma unroll
-      for (int k = 0; k < 3; ++k) q.v[k][i] = um[1 + k][i] * inv;
+      for (int k = 0; k < 3; ++k) {
+        q.m[k][i] = um[1 + k][i];
+        q.v[k][i] = um[1 + k][i] * inv;
+      }
       q.E[i] = um[4][i];
       q.p2[i] = pencil_p2(gm1, q.rho[i], q.v[0][i], q.v[1][i], q.v[2][i], q.E[i]);
       ok &= (q.rho[i] > 0.0) && (q.p2[i] > 0.0) && (q.p2[i] < 2.0e300) && (q.rho[i] < 1.0e300);
@@ -636,7 +643,7 @@ __device__ __forceinline__ void pencil_tile(PencilLds<N>& s, const StageArgs& a,
     const int x = X::template at<0>(bx, i);
     s.q[0][x] = q.rho[i];
 #pragma unroll
-    for (int k = 0; k < 3; ++k) s.q[1 + k][x] = q.v[k][i];
+    for (int k = 0; k < 3; ++k) s.q[1 + k][x] = q.m[k][i];
     s.q[4][x] = q.E[i];
   }
   pencil_sync<N>();
