@@ -122,8 +122,8 @@ __global__ __launch_bounds__(BUDGET, PERSIST ? 1 : 4) void k_batch_stage(BatchLa
 // 3 to 5, where the N = 4 and 5 runs of 24^3 hold most nodes: 9 602 us against 10 520 with every
 // run in k_batch_stage.
 template <int N, int EPI>
-__global__ __launch_bounds__((Pencil<N, EPI>::THREADS))
-__attribute__((amdgpu_waves_per_eu((Pencil<N, EPI>::WAVES), (Pencil<N, EPI>::WAVES))))
+__global__ __launch_bounds__((Pencil<N>::THREADS))
+__attribute__((amdgpu_waves_per_eu((Pencil<N>::WAVES), (Pencil<N>::WAVES))))
 void k_batch_pencil(BatchLaunch b, int cur, double A, double B, int emit, int kw) {
   __shared__ PencilLds<N> s;
   const int item = (int)xcd_tile(blockIdx.x, gridDim.x);
@@ -253,13 +253,13 @@ hipError_t batch_stage(hipStream_t st, const BatchLaunch& b, int budget, int gri
 bool batch_pencil_run(int N, int64_t E, int surf) { return use_pencil(N, E, surf); }
 
 int batch_pencil_elems(int N) {
-  return N == 3 ? Pencil<3, EPI_RK>::EB : (N == 4 ? Pencil<4, EPI_RK>::EB : Pencil<5, EPI_RK>::EB);
+  return N == 3 ? Pencil<3>::EB : (N == 4 ? Pencil<4>::EB : Pencil<5>::EB);
 }
 
 template <int N>
 static hipError_t pencil_launch(hipStream_t st, const BatchLaunch& b, int epi, int cur, double A,
                                 double B, int emit, int kw) {
-  const dim3 grid((unsigned)b.total), block(Pencil<N, EPI_RK>::THREADS);
+  const dim3 grid((unsigned)b.total), block(Pencil<N>::THREADS);
   if (epi == EPI_RK)
     hipLaunchKernelGGL((k_batch_pencil<N, EPI_RK>), grid, block, 0, st, b, cur, A, B, emit, kw);
   else

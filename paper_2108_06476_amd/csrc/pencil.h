@@ -20,7 +20,9 @@
 // line stays in registers for the x primitives and the update where they allow it; reading it
 // again cost more (N = 3, 64^3: 480 against 413 us per right-hand side).  Two waves per SIMD: at
 // three (168 VGPRs, N = 3) the compiler spills, and even 20 spilled registers cost more than the
-// third wave gives.
+// third wave gives; at one (N = 7, the conserved line held in AGPRs) near-equal states took 1 660 us
+// per step at 24^3, as with two, but every wait is exposed where pairs leave the near-equal series
+// (all of them: 3 590 against 2 130).
 #pragma once
 #include <hip/hip_runtime.h>
 
@@ -49,17 +51,18 @@ struct PencilMap {
   static constexpr bool FULL = EB * NL == THREADS;   // every thread has a line of its own
 };
 
-template <int N, int EPI>
+template <int N>
 struct Pencil : PencilMap<N> {
   static_assert(N >= 3 && N <= 7, "degrees with enough pairs per line");
-  // Waves per SIMD: two (256 registers).  N = 7 time steps: one (512, half of them AGPRs that
-  // hold values), so that the conserved line stays in registers; 24^3 1 684 us per step against
-  // 1 741 with two waves that read it three times (right-hand side alone: 257 against 236).
-  static constexpr int WAVES = N == 7 && EPI == EPI_RK ? 1 : 2;
-  static constexpr bool HOLD = N != 6 && (N != 7 || EPI == EPI_RK);   // the conserved home line
-                                          // stays in registers, or is read twice again
-  static constexpr bool PRE = N <= 4 || (N == 7 && HOLD);   // faces loaded a direction ahead
-  static constexpr int ROW = N <= 4 ? N + 1 : 3;   // pairs of a row whose means are formed together
+  static constexpr int WAVES = 2;   // per SIMD: 256 registers
+  static constexpr bool HOLD = N <= 5;   // the conserved home line stays in registers, or is read
+                                         // twice again
+  static constexpr bool PRE = N <= 4;    // faces loaded a direction ahead
+  // Pairs of a row whose means are formed together: as many as the registers hold.  More share the
+  // code of the middle and far branches, which at N = 7 is larger than the instruction cache
+  // (right-hand side at 24^3 with every pair in the middle branch: 370 us, 390 with three, 422 with
+  // two; N = 6 12^3 near-equal pairs 29.5, 31.0 with four).
+  static constexpr int ROW = N <= 4 ? N + 1 : N == 6 ? 3 : 4;
 };
 
 // LDS buffer: [variable][node of the block's (wave's) elements].
@@ -183,128 +186,145 @@ __device__ __forceinline__ double sconst(double c) {
   return c;
 }
 
-// artanh(z)/z on [0, 0.1] in x = z^2 (inv_ln_mean_mid's polynomial), coefficients in scalar
-// registers.
-__device__ __forceinline__ double artanh_q(double x) {
-  constexpr double kQ[11] = {1.0, 0.3333333333333325, 0.20000000000033863, 0.14285714280450776,
-                             0.11111111529834054, 0.09090889710268459, 0.07692864848122398,
-                             0.06656438300891282, 0.060018248406360414, 0.04412879698538037,
-                             0.0802184520988054};
-  double p = kQ[10];
-#pragma unroll
-  for (int k = 9; k > 0; --k) p = fma(p, x, sconst(kQ[k]));
-  return fma(p, x, 1.0);
-}
-
-// artanh(z)/z of the logarithmic means beyond the series: the polynomial below z^2 = 0.1, else
-// ln(r)/(2 z) with r = hi/lo = 2^k m, m in [1/sqrt 2, sqrt 2), ln r = k ln 2 + 2 s Q(s^2),
-// s = (m - 1)/(m + 1) (s^2 < 0.03).  NaN where r is not positive.
-__device__ __forceinline__ double artanh_far(double a, double b, double x) {
-  double y = x, k = 0.0, f = 1.0;
-  if (!(x < 0.1)) {
-    const double hi = fmax(a, b), lo = fmin(a, b);
-    const double r = hi * rcp_nr(lo);
-    double m = __builtin_amdgcn_frexp_mant(r);
-    int ex = __builtin_amdgcn_frexp_exp(r);
-    if (m < 0.7071067811865476) {
-      m *= 2.0;
-      ex -= 1;
-    }
-    const double sg = (m - 1.0) * rcp_nr(m + 1.0);
-    const double iz = (hi + lo) * rcp_nr(hi - lo);   // 1/z
-    f = sg * iz;
-    k = r > 0.0 ? (0.5 * 0.6931471805599453) * (double)ex * iz : __builtin_nan("");
-    y = sg * sg;
+// A step of a Horner scheme with the coefficient in scalar registers, set just before it (left to
+// the compiler it is moved to vector registers first; through sconst all of a polynomial's
+// coefficients are live at once and spill).
+struct HornerScalar {
+  __device__ __forceinline__ double operator()(double p, double x, double c) const {
+    double r;
+    asm("v_fma_f64 %0, %1, %2, %3" : "=v"(r) : "v"(p), "v"(x), "s"(c));
+    return r;
   }
-  return fma(f, artanh_q(y), k);
+};
+
+// a/b (b normal): the refined reciprocal and one residual correction.
+__device__ __forceinline__ double div_nr(double a, double b) {
+  const double r = rcp_nr(b), q = a * r;
+  return fma(fma(-b, q, a), r, q);
 }
 
-// The two logarithmic means of a pair for the lanes beyond the near-equal series.
+// (b - a)/ln(b/a) of a pair with z^2 >= 0.1, and its inverse: ln(hi/lo) = k ln 2 + 2 artanh s with
+// hi/lo = 2^k m, m in [1/sqrt 2, sqrt 2), s = (m - 1)/(m + 1) from the mantissas, whose difference is
+// exact.  NaN where a or b is not positive.
+__device__ __forceinline__ double pencil_ln_ratio(double hi, double lo) {
+  double mh = __builtin_amdgcn_frexp_mant(hi);
+  const double ml = __builtin_amdgcn_frexp_mant(lo);
+  int ex = __builtin_amdgcn_frexp_exp(hi) - __builtin_amdgcn_frexp_exp(lo);
+  const double sc = mh > 1.4142135623730951 * ml ? 0.5 : mh < 0.7071067811865476 * ml ? 2.0 : 1.0;
+  ex += sc == 0.5 ? 1 : sc == 2.0 ? -1 : 0;
+  mh *= sc;
+  const double s = (mh - ml) * rcp_nr(mh + ml);
+  const double l = fma(0.6931471805599453, (double)ex, s * inv_ln_mean_mid(s * s, HornerScalar()));
+  return lo > 0.0 ? l : __builtin_nan("");
+}
+
+// The two logarithmic means of a pair for the lanes beyond the polynomials.
 __device__ __forceinline__ void pencil_far(double a, double b, double c, double d, double& rl,
                                            double& ib) {
-  const double sr = a + b, zr = (b - a) * rcp_nr1(sr), xr = zr * zr;
-  const double qr = artanh_far(a, b, xr);
-  if (!(xr < 1.0e-4)) rl = 0.5 * sr * rcp_nr(qr);
-  const double sb = c + d, zb = (d - c) * rcp_nr1(sb), xb = zb * zb;
-  const double qb = artanh_far(c, d, xb);
-  if (!(xb < 1.0e-4)) ib = 2.0 * rcp_nr(sb) * qb;
+  const double zr = (b - a) * rcp_nr1(a + b), zb = (d - c) * rcp_nr1(c + d);
+  const double hr = fmax(a, b), lr = fmin(a, b), hb = fmax(c, d), lb = fmin(c, d);
+  if (!(zr * zr < 0.1)) rl = div_nr(hr - lr, pencil_ln_ratio(hr, lr));
+  if (!(zb * zb < 0.1)) ib = div_nr(pencil_ln_ratio(hb, lb), hb - lb);
+}
+
+// The logarithmic means rl = {{rho}}_ln and ib = 2/((gamma - 1) {{beta}}_ln) of the pairs (i, m), m
+// in [m0, m1), of a line; be: (gamma - 1) beta / 2 of the nodes.  The near-equal series serves all
+// lanes; a wave with a lane beyond it forms the polynomials of the middle branch as well, all pairs
+// of the row in flight together, and only one with a lane beyond z^2 = 0.1 takes the logarithm: a
+// loop over the pairs, one at a time at the head of the chunk, whose registers rotate, keeps the
+// code and the registers of that path small (park and unpark free registers meanwhile).
+template <int n, int ROW, typename Park, typename Unpark>
+__device__ __forceinline__ void pencil_means(double (&rho)[n], double (&be)[n], int i, int m0, int m1,
+                                             Park park, Unpark unpark, double (&rl)[ROW],
+                                             double (&ib)[ROW]) {
+  const double c1 = sconst(-1.0 / 6.0), c2 = sconst(-2.0 / 45.0), c3 = -22.0 / 945.0;
+  const double e1 = sconst(2.0 / 3.0), e2 = sconst(2.0 / 5.0), e3 = 2.0 / 7.0;
+  double xr[ROW], xb[ROW];
+  bool mid = false;
+#pragma unroll
+  for (int m = m0; m < m1; ++m) {
+    const int j = m - m0;
+    const double sr = rho[i] + rho[m], dr = rho[m] - rho[i];
+    const double zr = dr * rcp_nr1(sr);
+    const double sb = be[i] + be[m], db = be[m] - be[i];
+    const double rb = rcp_nr1(sb);
+    const double zb = db * rb;
+    xr[j] = zr * zr;
+    xb[j] = zb * zb;
+    rl[j] = sr * fma(xr[j], fma(xr[j], fma(xr[j], c3, c2), c1), 0.5);
+    ib[j] = rb * fma(xb[j], fma(xb[j], fma(xb[j], e3, e2), e1), 2.0);
+    mid |= !(xr[j] < 1.0e-4) | !(xb[j] < 1.0e-4);
+  }
+  if (__builtin_expect(__any(mid) != 0, 0)) {
+    bool far = false;
+#pragma unroll
+    for (int m = m0; m < m1; ++m) {
+      const int j = m - m0;
+      const double pr = (rho[i] + rho[m]) * ln_mean_mid(xr[j], HornerScalar());
+      const double pb = rcp_nr1(be[i] + be[m]) * inv_ln_mean_mid(xb[j], HornerScalar());
+      if (!(xr[j] < 1.0e-4)) rl[j] = pr;
+      if (!(xb[j] < 1.0e-4)) ib[j] = pb;
+      far |= !(xr[j] < 0.1) | !(xb[j] < 0.1);
+    }
+    if (__any(far)) {
+      park();
+#pragma unroll 1
+      for (int c = m0; c < m1; ++c) {
+        pencil_far(rho[i], rho[m0], be[i], be[m0], rl[0], ib[0]);
+        const double t0 = rho[m0], t1 = be[m0], t2 = rl[0], t3 = ib[0];
+#pragma unroll
+        for (int m = m0; m < m1 - 1; ++m) {
+          rho[m] = rho[m + 1];
+          be[m] = be[m + 1];
+          rl[m - m0] = rl[m - m0 + 1];
+          ib[m - m0] = ib[m - m0 + 1];
+        }
+        rho[m1 - 1] = t0;
+        be[m1 - 1] = t1;
+        rl[m1 - 1 - m0] = t2;
+        ib[m1 - 1 - m0] = t3;
+      }
+      unpark();
+    }
+  }
 }
 
 // Two-point fluxes of every pair of the line, contracted into acc (scaled as pencil_pair's).
-// be: (gamma - 1) beta / 2 of the nodes.  The near-equal series serves all lanes; where a lane
-// of the wave is beyond it, the row's means are formed again one pair at a time, in a loop
-// that keeps the code and the registers of that rare path small.  SC: every contribution times
-// dg (the share of the flux differencing where it is blended).
-template <int n, int ROW, bool SC, typename Park, typename Unpark>
+// be: (gamma - 1) beta / 2 of the nodes; SC: every contribution times dg (the share of the flux
+// differencing where it is blended).  Row I (pairs (I, m), m > I) in chunks of ROW pairs from M0 on,
+// then the rows after it: a recursion, not loops, which at n = 8 pass the compiler's limit on
+// unrolling and would leave the line in memory.
+template <int n, int ROW, bool SC, int I = 0, int M0 = 1, typename Park, typename Unpark>
 __device__ __forceinline__ void pencil_volume(PLine<n>& q, double (&be)[n], ConstTab S, double dg,
                                               Park park, Unpark unpark, double (&acc)[n][5]) {
-  const double c1 = sconst(-1.0 / 6.0), c2 = sconst(-2.0 / 45.0), c3 = -22.0 / 945.0;
-  const double e1 = sconst(2.0 / 3.0), e2 = sconst(2.0 / 5.0), e3 = 2.0 / 7.0;
+  constexpr int M1 = M0 + ROW < n ? M0 + ROW : n;
+  double rl[ROW], ib[ROW];
+  pencil_means<n, ROW>(q.rho, be, I, M0, M1, park, unpark, rl, ib);
 #pragma unroll
-  for (int i = 0; i < n - 1; ++i) {
+  for (int m = M0; m < M1; ++m) {
+    double f[5];
+    pencil_pair(rl[m - M0], ib[m - M0], q.v[0][I], q.v[1][I], q.v[2][I], q.p2[I], q.v[0][m],
+                q.v[1][m], q.v[2][m], q.p2[m], f);
+    double cim = S[I * TMAX + m], cmi = S[m * TMAX + I];
+    if constexpr (SC) {
+      cim *= dg;
+      cmi *= dg;
+    }
 #pragma unroll
-    for (int m0 = i + 1; m0 < n; m0 += ROW) {
-      const int m1 = m0 + ROW < n ? m0 + ROW : n;
-      double rl[ROW], ib[ROW];
-      bool far = false;
-#pragma unroll
-      for (int m = m0; m < m1; ++m) {
-        const double sr = q.rho[i] + q.rho[m], dr = q.rho[m] - q.rho[i];
-        const double zr = dr * rcp_nr1(sr), xr = zr * zr;
-        const double sb = be[i] + be[m], db = be[m] - be[i];
-        const double rb = rcp_nr1(sb);
-        const double zb = db * rb, xb = zb * zb;
-        rl[m - m0] = sr * fma(xr, fma(xr, fma(xr, c3, c2), c1), 0.5);
-        ib[m - m0] = rb * fma(xb, fma(xb, fma(xb, e3, e2), e1), 2.0);
-        far |= !(xr < 1.0e-4) | !(xb < 1.0e-4);
-      }
-      if (__builtin_expect(__any(far) != 0, 0)) {
-        // one pair at a time at the head of the chunk, whose registers rotate; park and
-        // unpark free registers meanwhile
-        park();
-#pragma unroll 1
-        for (int c = m0; c < m1; ++c) {
-          pencil_far(q.rho[i], q.rho[m0], be[i], be[m0], rl[0], ib[0]);
-          const double t0 = q.rho[m0], t1 = be[m0], t2 = rl[0], t3 = ib[0];
-#pragma unroll
-          for (int m = m0; m < m1 - 1; ++m) {
-            q.rho[m] = q.rho[m + 1];
-            be[m] = be[m + 1];
-            rl[m - m0] = rl[m - m0 + 1];
-            ib[m - m0] = ib[m - m0 + 1];
-          }
-          q.rho[m1 - 1] = t0;
-          be[m1 - 1] = t1;
-          rl[m1 - 1 - m0] = t2;
-          ib[m1 - 1 - m0] = t3;
-        }
-        unpark();
-      }
-#pragma unroll
-      for (int m = m0; m < m1; ++m) {
-        double f[5];
-        pencil_pair(rl[m - m0], ib[m - m0], q.v[0][i], q.v[1][i], q.v[2][i], q.p2[i], q.v[0][m],
-                    q.v[1][m], q.v[2][m], q.p2[m], f);
-        double cim = S[i * TMAX + m], cmi = S[m * TMAX + i];
-        if constexpr (SC) {
-          cim *= dg;
-          cmi *= dg;
-        }
-#pragma unroll
-        for (int v = 0; v < 5; ++v) {
-          acc[i][v] = fma(cim, f[v], acc[i][v]);
-          acc[m][v] = fma(cmi, f[v], acc[m][v]);
-        }
-      }
-      // the sums are formed here: sunk past the next rows they would keep every flux alive
-#pragma unroll
-      for (int v = 0; v < 5; ++v) {
-        asm("" : "+v"(acc[i][v]));
-#pragma unroll
-        for (int m = m0; m < m1; ++m) asm("" : "+v"(acc[m][v]));
-      }
+    for (int v = 0; v < 5; ++v) {
+      acc[I][v] = fma(cim, f[v], acc[I][v]);
+      acc[m][v] = fma(cmi, f[v], acc[m][v]);
     }
   }
+  // the sums are formed here: sunk past the next rows they would keep every flux alive
+#pragma unroll
+  for (int v = 0; v < 5; ++v) {
+    asm("" : "+v"(acc[I][v]));
+#pragma unroll
+    for (int m = M0; m < M1; ++m) asm("" : "+v"(acc[m][v]));
+  }
+  if constexpr (M1 < n) pencil_volume<n, ROW, SC, I, M1>(q, be, S, dg, park, unpark, acc);
+  else if constexpr (I + 2 < n) pencil_volume<n, ROW, SC, I + 1, I + 2>(q, be, S, dg, park, unpark, acc);
 }
 
 // Primitives of a face state: component k of the vectors along direction D + k.  Both sides of an
@@ -583,7 +603,7 @@ __device__ __forceinline__ double pencil_elem_speed(double* buf, ConstTab tab,
 template <int N, int EPI, bool SC>
 __device__ __forceinline__ void pencil_tile(PencilLds<N>& s, const StageArgs& a, const Geom& g,
                                             int tile) {
-  using P = Pencil<N, EPI>;
+  using P = Pencil<N>;
   using X = PencilPos<N>;
   constexpr int n = P::n, NL = P::NL, NN = P::NN;
   const PencilPlace<N> w(g, tile);
@@ -723,32 +743,45 @@ __device__ __forceinline__ void pencil_tile(PencilLds<N>& s, const StageArgs& a,
   } else {
     const double dt = a.dt_from ? stage_dt_from_partials(a) : *a.dt;
     const double dh = 0.5 * dt, dq = 0.25 * dt;
-    if constexpr (!P::HOLD) {
-      asm("" : "+v"(ho));
-      load_u();
-    }
-    double kv[5][n];
+    // N >= 4: a variable at a time; the loads of all five at once take the registers that the sums
+    // still hold (N = 7: 12 spilled, 24^3 1 737 us per step against 1 677; N = 6 12^3 206 / 189)
+    constexpr int STEP = N == 3 ? 5 : 1;
 #pragma unroll
-    for (int v = 0; v < 5; ++v)
+    for (int v0 = 0; v0 < 5; v0 += STEP) {
+      double kv[STEP][n];
+      if constexpr (!P::HOLD) asm("" : "+v"(ho));
+      if constexpr (!P::HOLD) {
 #pragma unroll
-      for (int i = 0; i < n; ++i) kv[v][i] = a.A != 0.0 ? ld(a.k + v * ENN, ho, i) : 0.0;
-    if (on) {
+        for (int v = v0; v < v0 + STEP; ++v)
 #pragma unroll
-      for (int v = 0; v < 5; ++v) {
+          for (int i = 0; i < n; ++i) um[v][i] = ld(a.uin + v * ENN, ho, i);
+      }
 #pragma unroll
-        for (int i = 0; i < n; ++i) kv[v][i] = fma(a.A, kv[v][i], (v == 0 ? dh : dq) * acc[i][v]);
-        if (a.kw) {
+      for (int v = v0; v < v0 + STEP; ++v)
 #pragma unroll
-          for (int i = 0; i < n; ++i) st(a.k + v * ENN, ho, i, kv[v][i]);
-        }
+        for (int i = 0; i < n; ++i) kv[v - v0][i] = a.A != 0.0 ? ld(a.k + v * ENN, ho, i) : 0.0;
+      if (on) {
 #pragma unroll
-        for (int i = 0; i < n; ++i) {
-          um[v][i] = fma(a.B, kv[v][i], um[v][i]);
-          if constexpr (N > 5) st(a.uout + v * ENN, ho, i, um[v][i]);
+        for (int v = v0; v < v0 + STEP; ++v) {
+          double (&k)[n] = kv[v - v0];
+#pragma unroll
+          for (int i = 0; i < n; ++i) k[i] = fma(a.A, k[i], (v == 0 ? dh : dq) * acc[i][v]);
+          if (a.kw) {
+#pragma unroll
+            for (int i = 0; i < n; ++i) st(a.k + v * ENN, ho, i, k[i]);
+          }
+#pragma unroll
+          for (int i = 0; i < n; ++i) {
+            um[v][i] = fma(a.B, k[i], um[v][i]);
+            if constexpr (N > 5) st(a.uout + v * ENN, ho, i, um[v][i]);
+          }
         }
       }
-      // (N = 6 and 7 gain nothing from streaming: 24^3 1 271 / 1 270 and 1 665 / 1 722)
-      if constexpr (N <= 5)
+      if constexpr (STEP < 5) phase_fence();
+    }
+    // (N = 6 and 7 gain nothing from streaming: 24^3 1 271 / 1 270 and 1 665 / 1 722)
+    if constexpr (N <= 5) {
+      if (on)
         store_out<5>(a.nt_out, [&](int v, auto nt) {
 #pragma unroll
           for (int i = 0; i < n; ++i) st_out(a.uout + v * ENN, ho, i, um[v][i], nt);
@@ -788,17 +821,24 @@ __device__ __forceinline__ void pencil_tile(PencilLds<N>& s, const StageArgs& a,
   }
 }
 
-// Meshes of k_pencil, by degree: below them a mesh has too few waves for the 2 048 that are
-// resident at a time (two per SIMD), and k_stage, with four to eight times as many, is the
-// faster.  TGV, microseconds per step, k_stage against k_pencil:
-//   N = 3: 24^3 176 / 181 (1.7 rounds of waves), 28^3 264 / 261, 32^3 382 / 328, 64^3 3 525 / 3 049
-//   N = 4: 20^3 219 / 236, 24^3 370 / 346, 40^3 1 808 / 1 700
-//   N = 5: 16^3 237 / 255, 19 x 23 x 13 320 / 301, 24^3 792 / 702, 36^3 2 613 / 2 238
-//   N = 6: 8^3 79 / 118, 10^3 173 / 152, 12^3 260 / 217, 24^3 1 857 / 1 262
-//   N = 7: 16^3 508 / 547, 24^3 1 824 / 1 684
-// Upper limit: byte offsets into a plane stay below 2^31 (k_stage's are 64 bits).
+// Meshes of k_pencil, by degree: below them k_stage, with four to eight times as many waves, is
+// the faster, on near-equal states or on those whose pairs leave the near-equal series, where a
+// line per thread gains less (its code grows past the instruction cache).  Microseconds per
+// adaptive step, k_stage / k_pencil, on TGV Mach 0.1 | TGV Mach 1 | random nodes within 10 %:
+//   N = 3: 28 x 28 x 27 242 / 233 | 251 / 254 | 272 / 266,  29^3 274 / 258 | 285 / 275 | 310 / 288,
+//          32^3 375 / 333 | 382 / 354 | 420 / 374,  64^3 3 526 / 3 008
+//   N = 4: 24^3 376 / 348 | 388 / 391 | 418 / 415,  26^3 452 / 412 | 457 / 448 | 509 / 482,
+//          28^3 625 / 570 | 642 / 599 | 685 / 621
+//   N = 5: 17 x 17 x 18 295 / 273 | 314 / 322 | 349 / 349,  18^3 320 / 290 | 342 / 338 | 380 / 367,
+//          20^3 428 / 368 | 458 / 447 | 510 / 484
+//   N = 6: 10^3 173 / 148 | 186 / 203 | 204 / 231,  11^3 214 / 181 | 227 / 223 | 249 / 255,
+//          12^3 260 / 197 | 280 / 238 | 308 / 270
+//   N = 7: 21 x 20 x 20 1 102 / 1 036 | 1 165 / 1 168 | 1 323 / 1 447,  21^3 1 235 / 1 149 |
+//          1 312 / 1 285 | 1 478 / 1 560,  23^3 1 594 / 1 467 | 1 684 / 1 636 | 1 924 / 1 918
+// The upper limit keeps the meshes beyond 2^28 nodes in k_stage, so that a state of 2^31 values can
+// be compared bit for bit with a small mesh's (one kernel for both; offsets here would reach 2^29).
 inline bool use_pencil(int N, int64_t E, int surf) {
-  constexpr int64_t min_E[5] = {20480, 12288, 5120, 960, 8192};   // N = 3..7
+  constexpr int64_t min_E[5] = {20480, 12288, 5832, 1331, 9261};   // N = 3..7
   if (N < 3 || N > 7 || (surf != SURF_LLF && surf != SURF_HLL)) return false;
   const int64_t nn = (int64_t)(N + 1) * (N + 1) * (N + 1);
   return E >= min_E[N - 3] && E * nn <= ((int64_t)1 << 28);
@@ -819,10 +859,10 @@ constexpr int64_t PENCIL_WIDE_E = 40960;
 
 // WPB: independent waves per block where a wave holds its elements whole, else 1.
 template <int N, int EPI, int WPB, bool SC = false>
-__global__ __launch_bounds__((Pencil<N, EPI>::THREADS * WPB))
-__attribute__((amdgpu_waves_per_eu((Pencil<N, EPI>::WAVES), (Pencil<N, EPI>::WAVES))))
+__global__ __launch_bounds__((Pencil<N>::THREADS * WPB))
+__attribute__((amdgpu_waves_per_eu((Pencil<N>::WAVES), (Pencil<N>::WAVES))))
 void k_pencil(StageArgs a, Geom g) {
-  using P = Pencil<N, EPI>;
+  using P = Pencil<N>;
   __shared__ PencilLds<N> s[WPB];
   const int w = P::WAVE ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) : 0;
   const int tile = (int)xcd_tile(blockIdx.x, gridDim.x) * WPB + w;

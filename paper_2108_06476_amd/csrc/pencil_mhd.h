@@ -286,8 +286,6 @@ __device__ __forceinline__ void mhd_weak_line(double gm1, const MLine<n>& q, Con
 template <int n, typename Park, typename Unpark>
 __device__ __forceinline__ void mhd_ec_line(double gm1, MLine<n>& q, ConstTab S, Park park,
                                             Unpark unpark, double (&acc)[n][8]) {
-  const double c1 = sconst(-1.0 / 6.0), c2 = sconst(-2.0 / 45.0), c3 = -22.0 / 945.0;
-  const double e1 = sconst(2.0 / 3.0), e2 = sconst(2.0 / 5.0), e3 = 2.0 / 7.0;
   double be[n], v2[n], B2[n], vB[n], pw[n];
 #pragma unroll
   for (int m = 0; m < n; ++m) {
@@ -313,44 +311,13 @@ __device__ __forceinline__ void mhd_ec_line(double gm1, MLine<n>& q, ConstTab S,
   };
 #pragma unroll
   for (int i = 0; i < n - 1; ++i) {
-    double rl[n], ib[n];
-    bool far = false;
-#pragma unroll
-    for (int m = i + 1; m < n; ++m) {
-      const double sr = q.rho[i] + q.rho[m], dr = q.rho[m] - q.rho[i];
-      const double zr = dr * rcp_nr1(sr), xr = zr * zr;
-      const double sb = be[i] + be[m], db = be[m] - be[i];
-      const double rb = rcp_nr1(sb);
-      const double zb = db * rb, xb = zb * zb;
-      rl[m] = sr * fma(xr, fma(xr, fma(xr, c3, c2), c1), 0.5);
-      ib[m] = rb * fma(xb, fma(xb, fma(xb, e3, e2), e1), 2.0);
-      far |= !(xr < 1.0e-4) | !(xb < 1.0e-4);
-    }
-    if (__builtin_expect(__any(far) != 0, 0)) {   // as pencil_volume's
-      park();
-#pragma unroll 1
-      for (int c = i + 1; c < n; ++c) {
-        pencil_far(q.rho[i], q.rho[i + 1], be[i], be[i + 1], rl[i + 1], ib[i + 1]);
-        const double t0 = q.rho[i + 1], t1 = be[i + 1], t2 = rl[i + 1], t3 = ib[i + 1];
-#pragma unroll
-        for (int m = i + 1; m < n - 1; ++m) {
-          q.rho[m] = q.rho[m + 1];
-          be[m] = be[m + 1];
-          rl[m] = rl[m + 1];
-          ib[m] = ib[m + 1];
-        }
-        q.rho[n - 1] = t0;
-        be[n - 1] = t1;
-        rl[n - 1] = t2;
-        ib[n - 1] = t3;
-      }
-      unpark();
-    }
+    double rl[n], ib[n];   // of the pair (i, m) at m - i - 1
+    pencil_means<n, n>(q.rho, be, i, i + 1, n, park, unpark, rl, ib);
 #pragma unroll
     for (int m = i + 1; m < n; ++m) {
       double f[8];
       const MPoint L = point(i), R = point(m);
-      mpair_flux(L, be[i], R, be[m], rl[m], ib[m], rcp_nr(be[i] + be[m]), gm1, f);
+      mpair_flux(L, be[i], R, be[m], rl[m - i - 1], ib[m - i - 1], rcp_nr(be[i] + be[m]), gm1, f);
       const double cim = S[i * TMAX + m], cmi = S[m * TMAX + i];
 #pragma unroll
       for (int v = 0; v < 8; ++v) {

@@ -64,8 +64,14 @@ __device__ __forceinline__ double sqrt_pos1(double x) {
 // P(x) = z/(2 artanh z) and 2Q(x) = 2 artanh(z)/z, the interpolants at Chebyshev nodes of
 // [0, 0.1] formed at 60 digits (logmean_fit.py beside this file).  Both are analytic for
 // |x| < 1, so ten degrees leave about 1e-18 relative error with these float64 coefficients,
-// and neither needs a reciprocal or a logarithm.
-__device__ __forceinline__ double ln_mean_mid(double x) {
+// and neither needs a reciprocal or a logarithm.  step(p, x, c): p x + c, one step of the Horner
+// scheme (a kernel may choose where the coefficient is held).
+struct HornerStep {
+  __device__ __forceinline__ double operator()(double p, double x, double c) const { return fma(p, x, c); }
+};
+
+template <typename Step = HornerStep>
+__device__ __forceinline__ double ln_mean_mid(double x, Step step = Step()) {
   constexpr double kP[11] = {
       0.5, -0.1666666666666666, -0.04444444444447207, -0.023280423276128673,
       -0.015097002105376345, -0.010898386189257736, -0.008394230906424155,
@@ -73,11 +79,12 @@ __device__ __forceinline__ double ln_mean_mid(double x) {
       -0.006793753103187953};
   double p = kP[10];
 #pragma unroll
-  for (int k = 9; k >= 0; --k) p = fma(p, x, kP[k]);
+  for (int k = 9; k >= 0; --k) p = step(p, x, kP[k]);
   return p;
 }
 
-__device__ __forceinline__ double inv_ln_mean_mid(double x) {
+template <typename Step = HornerStep>
+__device__ __forceinline__ double inv_ln_mean_mid(double x, Step step = Step()) {
   constexpr double kQ[11] = {   // Q(x) = artanh(z)/z; the factor 2 is applied exactly below
       1.0, 0.3333333333333325, 0.20000000000033863, 0.14285714280450776,
       0.11111111529834054, 0.09090889710268459, 0.07692864848122398,
@@ -85,7 +92,7 @@ __device__ __forceinline__ double inv_ln_mean_mid(double x) {
       0.0802184520988054};
   double p = 2.0 * kQ[10];
 #pragma unroll
-  for (int k = 9; k >= 0; --k) p = fma(p, x, 2.0 * kQ[k]);
+  for (int k = 9; k >= 0; --k) p = step(p, x, 2.0 * kQ[k]);
   return p;
 }
 

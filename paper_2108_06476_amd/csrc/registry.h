@@ -75,9 +75,9 @@ struct Launch {
 
   template <int EPI, int WPB, bool SC = false>
   static hipError_t pencil1(hipStream_t st, const StageArgs& a, const Geom& g) {
-    constexpr int per = Pencil<N, EPI>::EB * WPB;   // elements per block
+    constexpr int per = Pencil<N>::EB * WPB;   // elements per block
     hipLaunchKernelGGL((k_pencil<N, EPI, WPB, SC>), dim3((unsigned)((g.E + per - 1) / per)),
-                       dim3(Pencil<N, EPI>::THREADS * WPB), 0, st, a, g);
+                       dim3(Pencil<N>::THREADS * WPB), 0, st, a, g);
     return hipGetLastError();
   }
 

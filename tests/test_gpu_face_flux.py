@@ -24,7 +24,7 @@ from gpu_util import dev, host
 
 pytestmark = pytest.mark.gpu
 
-CELLS = {3: (32, 32, 20), 4: (24, 23, 23), 5: (19, 17, 16), 6: (12, 9, 9), 7: (21, 20, 20)}
+CELLS = {3: (32, 32, 20), 4: (28, 27, 27), 5: (19, 18, 18), 6: (12, 12, 11), 7: (22, 21, 21)}
 
 
 def _state(xyz, cells, seed):
