@@ -197,8 +197,8 @@ __device__ __forceinline__ void mpair_flux(const MPoint& L, double beL, const MP
 __device__ __forceinline__ void mpair_means(double gm1, const MPoint& L, const MPoint& R,
                                             double& beL, double& beR, double& rl, double& ib,
                                             double& rb) {
-  beL = 0.25 * gm1 * L.rho * rcp_nr1(L.p);
-  beR = 0.25 * gm1 * R.rho * rcp_nr1(R.p);
+  beL = 0.25 * gm1 * L.rho * rcp_nr(L.p);
+  beR = 0.25 * gm1 * R.rho * rcp_nr(R.p);
   rl = ln_mean<false>(L.rho, R.rho);
   ib = inv_ln_mean<false>(beL, beR);
   rb = rcp_nr(beL + beR);
@@ -290,7 +290,7 @@ __device__ __forceinline__ void mhd_ec_line(double gm1, MLine<n>& q, ConstTab S,
 #pragma unroll
   for (int m = 0; m < n; ++m) {
     const MPoint a = mhd_line_point<n>(gm1, q, m);
-    be[m] = (0.25 * gm1 * a.rho) * rcp_nr1(a.p);
+    be[m] = (0.25 * gm1 * a.rho) * rcp_nr(a.p);
     v2[m] = a.v2;
     B2[m] = a.B2;
     vB[m] = a.vB;
