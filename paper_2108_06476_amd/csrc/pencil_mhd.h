@@ -9,16 +9,17 @@
 
 namespace dgx {
 
-// LDS buffer: rho, v, E, B of the tile's nodes; then sums.
+// LDS buffer: the states (rho, m, E, B) of the tile's nodes; then sums.
 template <int N>
 struct MhdPencilLds {
   double q[8][PencilMap<N>::EB * PencilMap<N>::NN];
 };
 
-// A line's nodes; vectors in the order D, D + 1, D + 2 of the line's direction D.
+// A line's nodes; vectors in the order D, D + 1, D + 2 of the line's direction D.  The momentum is
+// kept as it is stored (see PLine).
 template <int n>
 struct MLine {
-  double rho[n], v[3][n], E[n], B[3][n];
+  double rho[n], m[3][n], v[3][n], E[n], B[3][n];
 };
 
 // Plane of the buffer (and of a state) that holds component c of (rho, v or m, E, B) for a line
@@ -35,9 +36,11 @@ __device__ __forceinline__ void mhd_line_read(const MhdPencilLds<N>& s, int bl, 
     const int x = PencilPos<N>::template at<D>(bl, m);
     q.rho[m] = s.q[0][x];
     q.E[m] = s.q[4][x];
+    const double inv = rcp_nr(q.rho[m]);
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
-      q.v[k][m] = s.q[mhd_plane<D>(1 + k)][x];
+      q.m[k][m] = s.q[mhd_plane<D>(1 + k)][x];
+      q.v[k][m] = q.m[k][m] * inv;
       q.B[k][m] = s.q[mhd_plane<D>(5 + k)][x];
     }
   }
@@ -81,11 +84,11 @@ __device__ __forceinline__ void mhd_face_load(const double* __restrict__ u, cons
 
 // Pointwise values of one node of a line.
 struct MPoint {
-  double rho, inv, v[3], E, B[3], p, v2, B2, vB;
+  double rho, inv, m[3], v[3], E, B[3], p, v2, B2, vB;
 };
 
-__device__ __forceinline__ MPoint mhd_point(double gm1, double rho, const double (&v)[3], double E,
-                                            const double (&B)[3]) {
+__device__ __forceinline__ MPoint mhd_point(double gm1, double rho, const double (&m)[3],
+                                            const double (&v)[3], double E, const double (&B)[3]) {
   MPoint a;
   a.rho = rho;
   a.inv = 0.0;
@@ -93,6 +96,7 @@ __device__ __forceinline__ MPoint mhd_point(double gm1, double rho, const double
   a.v2 = a.B2 = a.vB = 0.0;
 #pragma unroll
   for (int k = 0; k < 3; ++k) {
+    a.m[k] = m[k];
     a.v[k] = v[k];
     a.B[k] = B[k];
     a.v2 += v[k] * v[k];
@@ -109,7 +113,7 @@ __device__ __forceinline__ bool mhd_physical(const MPoint& a) {
 
 // Physical flux along the line; the normal field's flux is zero.
 __device__ __forceinline__ void mpoint_flux(const MPoint& a, double (&f)[8]) {
-  const double m = a.rho * a.v[0], pt = a.p + 0.5 * a.B2;
+  const double m = a.m[0], pt = a.p + 0.5 * a.B2;
   f[0] = m;
   f[1] = m * a.v[0] + (pt - a.B[0] * a.B[0]);
   f[2] = m * a.v[1] - a.B[0] * a.B[1];
@@ -140,7 +144,7 @@ __device__ __forceinline__ double mpoint_surface_flux(int surf, double gamma, co
   du[4] = R.E - L.E;
 #pragma unroll
   for (int k = 0; k < 3; ++k) {
-    du[1 + k] = R.rho * R.v[k] - L.rho * L.v[k];
+    du[1 + k] = R.m[k] - L.m[k];
     du[5 + k] = R.B[k] - L.B[k];
   }
   const double cL = mpoint_cf(L, gamma, 0), cR = mpoint_cf(R, gamma, 0);
@@ -206,8 +210,8 @@ __device__ __forceinline__ void mpair_means(double gm1, const MPoint& L, const M
 
 template <int n>
 __device__ __forceinline__ MPoint mhd_line_point(double gm1, const MLine<n>& q, int m) {
-  return mhd_point(gm1, q.rho[m], {q.v[0][m], q.v[1][m], q.v[2][m]}, q.E[m],
-                   {q.B[0][m], q.B[1][m], q.B[2][m]});
+  return mhd_point(gm1, q.rho[m], {q.m[0][m], q.m[1][m], q.m[2][m]},
+                   {q.v[0][m], q.v[1][m], q.v[2][m]}, q.E[m], {q.B[0][m], q.B[1][m], q.B[2][m]});
 }
 
 // Lifted face terms at the two ends of a line: f[0] minus, f[1] plus (scaled as the volume's sums
@@ -220,7 +224,8 @@ __device__ __forceinline__ void mhd_faces(const Geom& g, int surf, ConstTab lift
   for (int s = 0; s < 2; ++s) {
     MPoint me = mhd_line_point<n>(gm1, q, s == 0 ? 0 : n - 1);
     const double inv = rcp_nr(un[s][0]);
-    MPoint nb = mhd_point(gm1, un[s][0], {un[s][1] * inv, un[s][2] * inv, un[s][3] * inv}, un[s][4],
+    MPoint nb = mhd_point(gm1, un[s][0], {un[s][1], un[s][2], un[s][3]},
+                          {un[s][1] * inv, un[s][2] * inv, un[s][3] * inv}, un[s][4],
                           {un[s][5], un[s][6], un[s][7]});
     if (!mhd_physical(nb)) *g.flag = 1;
     double F[8], cf = 1.0;
@@ -378,6 +383,7 @@ __device__ __forceinline__ void mhd_pencil_tile(MhdPencilLds<N>& s, const StageA
       q.E[i] = um[4][i];
 #pragma unroll
       for (int k = 0; k < 3; ++k) {
+        q.m[k][i] = um[1 + k][i];
         q.v[k][i] = um[1 + k][i] * inv;
         q.B[k][i] = um[5 + k][i];
       }
@@ -407,7 +413,7 @@ __device__ __forceinline__ void mhd_pencil_tile(MhdPencilLds<N>& s, const StageA
     s.q[4][x] = q.E[i];
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
-      s.q[1 + k][x] = q.v[k][i];
+      s.q[1 + k][x] = q.m[k][i];
       s.q[5 + k][x] = q.B[k][i];
     }
   }
@@ -510,8 +516,9 @@ __device__ __forceinline__ void mhd_pencil_tile(MhdPencilLds<N>& s, const StageA
 #pragma unroll
       for (int i = 0; i < n; ++i) {
         const double inv = rcp_nr(um[0][i]);
-        MPoint pt = mhd_point(gm1, um[0][i], {um[1][i] * inv, um[2][i] * inv, um[3][i] * inv},
-                              um[4][i], {um[5][i], um[6][i], um[7][i]});
+        MPoint pt = mhd_point(gm1, um[0][i], {um[1][i], um[2][i], um[3][i]},
+                              {um[1][i] * inv, um[2][i] * inv, um[3][i] * inv}, um[4][i],
+                              {um[5][i], um[6][i], um[7][i]});
         pt.inv = inv;
         ok &= mhd_physical(pt);
 #pragma unroll
