@@ -743,41 +743,40 @@ __device__ __forceinline__ void pencil_tile(PencilLds<N>& s, const StageArgs& a,
   } else {
     const double dt = a.dt_from ? stage_dt_from_partials(a) : *a.dt;
     const double dh = 0.5 * dt, dq = 0.25 * dt;
-    // N >= 4: a variable at a time; the loads of all five at once take the registers that the sums
-    // still hold (N = 7: 12 spilled, 24^3 1 737 us per step against 1 677; N = 6 12^3 206 / 189)
-    constexpr int STEP = N == 3 ? 5 : 1;
-#pragma unroll
-    for (int v0 = 0; v0 < 5; v0 += STEP) {
-      double kv[STEP][n];
-      if constexpr (!P::HOLD) asm("" : "+v"(ho));
+    // Variables whose loads are in flight at once.  N = 6 and 7: one; what the sums still hold leaves
+    // no registers for more (N = 6 12^3 188 us per step, 193 with two, 204 with five; 24^3 1 250,
+    // 1 260, 1 267).  N = 5: three (19 x 23 x 13 287, 292 with five).
+    constexpr int DEPTH = N <= 4 ? 5 : N == 5 ? 3 : 1;
+    double kv[DEPTH][n];
+    auto load = [&](int v) {
       if constexpr (!P::HOLD) {
+        asm("" : "+v"(ho));
 #pragma unroll
-        for (int v = v0; v < v0 + STEP; ++v)
-#pragma unroll
-          for (int i = 0; i < n; ++i) um[v][i] = ld(a.uin + v * ENN, ho, i);
+        for (int i = 0; i < n; ++i) um[v][i] = ld(a.uin + v * ENN, ho, i);
       }
 #pragma unroll
-      for (int v = v0; v < v0 + STEP; ++v)
+      for (int i = 0; i < n; ++i) kv[v % DEPTH][i] = a.A != 0.0 ? ld(a.k + v * ENN, ho, i) : 0.0;
+    };
 #pragma unroll
-        for (int i = 0; i < n; ++i) kv[v - v0][i] = a.A != 0.0 ? ld(a.k + v * ENN, ho, i) : 0.0;
+    for (int v = 0; v < DEPTH; ++v) load(v);
+#pragma unroll
+    for (int v = 0; v < 5; ++v) {
+      if constexpr (DEPTH < 5) phase_fence();
       if (on) {
+        double (&k)[n] = kv[v % DEPTH];
 #pragma unroll
-        for (int v = v0; v < v0 + STEP; ++v) {
-          double (&k)[n] = kv[v - v0];
+        for (int i = 0; i < n; ++i) k[i] = fma(a.A, k[i], (v == 0 ? dh : dq) * acc[i][v]);
+        if (a.kw) {
 #pragma unroll
-          for (int i = 0; i < n; ++i) k[i] = fma(a.A, k[i], (v == 0 ? dh : dq) * acc[i][v]);
-          if (a.kw) {
+          for (int i = 0; i < n; ++i) st(a.k + v * ENN, ho, i, k[i]);
+        }
 #pragma unroll
-            for (int i = 0; i < n; ++i) st(a.k + v * ENN, ho, i, k[i]);
-          }
-#pragma unroll
-          for (int i = 0; i < n; ++i) {
-            um[v][i] = fma(a.B, k[i], um[v][i]);
-            if constexpr (N > 5) st(a.uout + v * ENN, ho, i, um[v][i]);
-          }
+        for (int i = 0; i < n; ++i) {
+          um[v][i] = fma(a.B, k[i], um[v][i]);
+          if constexpr (N > 5) st(a.uout + v * ENN, ho, i, um[v][i]);
         }
       }
-      if constexpr (STEP < 5) phase_fence();
+      if (v + DEPTH < 5) load(v + DEPTH);
     }
     // (N = 6 and 7 gain nothing from streaming: 24^3 1 271 / 1 270 and 1 665 / 1 722)
     if constexpr (N <= 5) {
@@ -821,16 +820,17 @@ __device__ __forceinline__ void pencil_tile(PencilLds<N>& s, const StageArgs& a,
   }
 }
 
-// Meshes of k_pencil, by degree: below them k_stage, with four to eight times as many waves, is
-// the faster, on near-equal states or on those whose pairs leave the near-equal series, where a
-// line per thread gains less (its code grows past the instruction cache).  Microseconds per
-// adaptive step, k_stage / k_pencil, on TGV Mach 0.1 | TGV Mach 1 | random nodes within 10 %:
+// Meshes of k_pencil, by degree: about where a line per thread is the faster on near-equal states
+// and on those whose pairs leave the near-equal series, where it gains less (its code grows past the
+// instruction cache).  Microseconds per adaptive step, k_stage / k_pencil, on TGV Mach 0.1 | TGV
+// Mach 1 | random nodes within 10 %:
 //   N = 3: 28 x 28 x 27 242 / 233 | 251 / 254 | 272 / 266,  29^3 274 / 258 | 285 / 275 | 310 / 288,
 //          32^3 375 / 333 | 382 / 354 | 420 / 374,  64^3 3 526 / 3 008
-//   N = 4: 24^3 376 / 348 | 388 / 391 | 418 / 415,  26^3 452 / 412 | 457 / 448 | 509 / 482,
-//          28^3 625 / 570 | 642 / 599 | 685 / 621
+//   N = 4: 23 x 23 x 24 322 / 317 | 338 / 354 | 368 / 375,  24^3 376 / 348 | 388 / 391 | 418 / 415,
+//          26^3 452 / 412 | 457 / 448 | 509 / 482,  28^3 625 / 570 | 642 / 599 | 685 / 621
+//          (in ensembles 24^3 gains more: two such runs 1.10, eight runs with two of them 1.09)
 //   N = 5: 17 x 17 x 18 295 / 273 | 314 / 322 | 349 / 349,  18^3 320 / 290 | 342 / 338 | 380 / 367,
-//          20^3 428 / 368 | 458 / 447 | 510 / 484
+//          19 x 23 x 13 343 / 292,  20^3 428 / 368 | 458 / 447 | 510 / 484
 //   N = 6: 10^3 173 / 148 | 186 / 203 | 204 / 231,  11^3 214 / 181 | 227 / 223 | 249 / 255,
 //          12^3 260 / 197 | 280 / 238 | 308 / 270
 //   N = 7: 21 x 20 x 20 1 102 / 1 036 | 1 165 / 1 168 | 1 323 / 1 447,  21^3 1 235 / 1 149 |
@@ -838,7 +838,7 @@ __device__ __forceinline__ void pencil_tile(PencilLds<N>& s, const StageArgs& a,
 // The upper limit keeps the meshes beyond 2^28 nodes in k_stage, so that a state of 2^31 values can
 // be compared bit for bit with a small mesh's (one kernel for both; offsets here would reach 2^29).
 inline bool use_pencil(int N, int64_t E, int surf) {
-  constexpr int64_t min_E[5] = {20480, 12288, 5832, 1331, 9261};   // N = 3..7
+  constexpr int64_t min_E[5] = {20480, 13500, 5400, 1331, 9261};   // N = 3..7
   if (N < 3 || N > 7 || (surf != SURF_LLF && surf != SURF_HLL)) return false;
   const int64_t nn = (int64_t)(N + 1) * (N + 1) * (N + 1);
   return E >= min_E[N - 3] && E * nn <= ((int64_t)1 << 28);
