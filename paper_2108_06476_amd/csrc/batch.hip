@@ -48,13 +48,18 @@ struct dgx_batch_s {
   int budget = 256;
   int grid = 0;       // blocks of the TILED launch
   int cus = 0;
-  // recording of the steps' graph: the main branch and one for each further group
+  std::vector<int> groups;   // the groups that hold runs, in the order of their branches
+  // recording of the steps' graphs: the main branch and one for each group after the first
   hipStream_t cap = nullptr;
   hipStream_t side[GROUPS] = {};
   hipEvent_t fork = nullptr, joined[GROUPS] = {};
-  hipGraph_t graph = nullptr;
-  hipGraphExec_t gexec = nullptr;
-  double graph_cfl = -1.0;
+  // [0]: the last step of an odd count, [1]: two steps; each for the cfl it was recorded with
+  struct Steps {
+    hipGraph_t graph = nullptr;
+    hipGraphExec_t exec = nullptr;
+    double cfl = -1.0;
+  } steps[2];
+  double odd_cfl = -1.0;   // the last odd count's
   std::string err;
 };
 
@@ -100,11 +105,11 @@ bool dev_ok(const void* p, size_t bytes) {
 }
 
 void drop_graph(dgx_batch b) {
-  if (b->gexec) (void)hipGraphExecDestroy(b->gexec);
-  if (b->graph) (void)hipGraphDestroy(b->graph);
-  b->gexec = nullptr;
-  b->graph = nullptr;
-  b->graph_cfl = -1.0;
+  for (dgx_batch_s::Steps& g : b->steps) {
+    if (g.exec) (void)hipGraphExecDestroy(g.exec);
+    if (g.graph) (void)hipGraphDestroy(g.graph);
+    g = dgx_batch_s::Steps();
+  }
 }
 
 // The device lists of a group: its runs' tile counts for `elems(N)` elements per tile.
@@ -157,16 +162,6 @@ dgx_status enqueue_group(dgx_batch b, hipStream_t st, int gi, int epi, int cur, 
   return DGX_OK;
 }
 
-// One RK stage (or right-hand side) of every run.
-dgx_status enqueue_stage(dgx_batch b, hipStream_t st, int epi, int cur, double A, double B,
-                         int emit, int kw) {
-  for (int gi = dgx_batch_s::TILED; gi < dgx_batch_s::GROUPS; ++gi) {
-    dgx_status r = enqueue_group(b, st, gi, epi, cur, A, B, emit, kw);
-    if (r != DGX_OK) return r;
-  }
-  return DGX_OK;
-}
-
 dgx_status upload_desc(dgx_batch b) {
   // work already enqueued may still read the descriptors
   BHIP(b, hipStreamSynchronize(b->stream));
@@ -197,65 +192,93 @@ dgx_status bind(dgx_batch b, double* const* u, double* const* du, double* t) {
   return DGX_OK;
 }
 
-// The five stages of a step.  branch: st records a graph, and each group's stages become a branch
-// of it (the groups share no run).  Branches fill each other's last rounds of blocks, where a
-// chain of all launches in turn leaves compute units idle at the end of each.  Two steps, chain /
-// branches, microseconds: 13 runs (one in lines, N = 4 24^3) 2 490 / 2 265, 9 runs 1 775 / 1 530,
-// 12 runs (three in lines, N = 4 and 5) 5 350 / 5 100, 4 runs 2 550 / 2 150; 32 runs (six in
-// lines), where every launch has many rounds, 9 495 / 9 515.
+// Streams and events of the graphs' branches.
+dgx_status ensure_branches(dgx_batch b) {
+  if (!b->fork) BHIP(b, hipEventCreateWithFlags(&b->fork, hipEventDisableTiming));
+  for (size_t i = 1; i < b->groups.size(); ++i) {
+    const int gi = b->groups[i];
+    if (!b->side[gi]) BHIP(b, hipStreamCreateWithFlags(&b->side[gi], hipStreamNonBlocking));
+    if (!b->joined[gi]) BHIP(b, hipEventCreateWithFlags(&b->joined[gi], hipEventDisableTiming));
+  }
+  return DGX_OK;
+}
+
+// work(group, stream) for every group in turn on st, or (branch: st records a graph) the first on st
+// and each other one on a branch that leaves st here and comes back to it (the groups share no run).
+// Branches fill each other's last rounds of blocks, where launches in turn leave compute units idle
+// at the end of each.
+template <typename Work>
+dgx_status branch_groups(dgx_batch b, hipStream_t st, bool branch, Work work) {
+  const size_t ng = b->groups.size();
+  branch = branch && ng > 1;
+  if (branch) BHIP(b, hipEventRecord(b->fork, st));
+  dgx_status r = DGX_OK;
+  for (size_t i = 0; i < ng; ++i) {
+    const int gi = b->groups[i];
+    hipStream_t sg = branch && i > 0 ? b->side[gi] : st;
+    if (sg != st) BHIP(b, hipStreamWaitEvent(sg, b->fork, 0));
+    if (r == DGX_OK) r = work(gi, sg);
+    if (sg != st) BHIP(b, hipEventRecord(b->joined[gi], sg));   // (also after a failed launch)
+  }
+  for (size_t i = 1; branch && i < ng; ++i)
+    BHIP(b, hipStreamWaitEvent(st, b->joined[b->groups[i]], 0));
+  return r;
+}
+
+// The time steps and the five stages of a step, a branch per group (in a graph) or the groups in turn.
 dgx_status enqueue_step(dgx_batch b, hipStream_t st, double cfl, int cur, bool emit, bool branch) {
   BHIP(b, batch_dt(st, b->desc_d, b->nruns, cfl));
-  bool first = true;
-  std::vector<int> forked;
-  if (branch) BHIP(b, hipEventRecord(b->fork, st));
-  for (int gi = dgx_batch_s::TILED; gi < dgx_batch_s::GROUPS; ++gi) {
-    if (b->bl[gi].total == 0) continue;
-    hipStream_t sg = branch && !first ? b->side[gi] : st;
-    first = false;
-    if (sg != st) BHIP(b, hipStreamWaitEvent(sg, b->fork, 0));
+  return branch_groups(b, st, branch, [&](int gi, hipStream_t sg) {
     for (int s = 0, c = cur; s < 5; ++s, c = 1 - c) {
       dgx_status r = enqueue_group(b, sg, gi, EPI_RK, c, CK_A[s], CK_B[s], (emit && s == 4) ? 1 : 0, s < 4);
       if (r != DGX_OK) return r;
     }
-    if (sg != st) {
-      BHIP(b, hipEventRecord(b->joined[gi], sg));
-      forked.push_back(gi);
-    }
-  }
-  for (int gi : forked) BHIP(b, hipStreamWaitEvent(st, b->joined[gi], 0));
-  return DGX_OK;
+    return DGX_OK;
+  });
 }
 
-// Two steps: the state returns to the caller's buffer (10 stages).  The second step's
-// last stage emits the wave speeds of the next step, so the graph can be replayed.
-dgx_status enqueue_two_steps(dgx_batch b, hipStream_t st, double cfl) {
-  dgx_status r = enqueue_step(b, st, cfl, 0, true, true);
-  return r == DGX_OK ? enqueue_step(b, st, cfl, 1, true, true) : r;
-}
-
-dgx_status ensure_graph(dgx_batch b, double cfl) {
-  if (b->gexec && b->graph_cfl == cfl) return DGX_OK;
-  drop_graph(b);
+// The graph of one step, or of two: the state returns to the caller's buffer (10 stages), and the
+// second step's last stage emits the wave speeds of the next, so that it can be replayed.
+dgx_status ensure_graph(dgx_batch b, int nsteps, double cfl) {
+  dgx_batch_s::Steps& g = b->steps[nsteps - 1];
+  if (g.exec && g.cfl == cfl) return DGX_OK;
+  if (g.exec) (void)hipGraphExecDestroy(g.exec);
+  if (g.graph) (void)hipGraphDestroy(g.graph);
+  g = dgx_batch_s::Steps();
   if (!b->cap) BHIP(b, hipStreamCreateWithFlags(&b->cap, hipStreamNonBlocking));
-  if (!b->fork) BHIP(b, hipEventCreateWithFlags(&b->fork, hipEventDisableTiming));
-  for (int gi = dgx_batch_s::PENCIL; gi < dgx_batch_s::GROUPS; ++gi) {
-    if (b->bl[gi].total == 0) continue;
-    if (!b->side[gi]) BHIP(b, hipStreamCreateWithFlags(&b->side[gi], hipStreamNonBlocking));
-    if (!b->joined[gi]) BHIP(b, hipEventCreateWithFlags(&b->joined[gi], hipEventDisableTiming));
-  }
+  dgx_status st = ensure_branches(b);
+  if (st != DGX_OK) return st;
   BHIP(b, hipStreamBeginCapture(b->cap, hipStreamCaptureModeThreadLocal));
-  dgx_status st = enqueue_two_steps(b, b->cap, cfl);
-  hipGraph_t g = nullptr;
-  hipError_t e = hipStreamEndCapture(b->cap, &g);
-  if (st != DGX_OK) {
-    if (g) (void)hipGraphDestroy(g);
-    return st;
+  st = enqueue_step(b, b->cap, cfl, 0, nsteps == 2, true);
+  if (st == DGX_OK && nsteps == 2) st = enqueue_step(b, b->cap, cfl, 1, true, true);
+  hipGraph_t graph = nullptr;
+  hipError_t e = hipStreamEndCapture(b->cap, &graph);
+  if (st != DGX_OK || e != hipSuccess) {
+    if (graph) (void)hipGraphDestroy(graph);
+    return st != DGX_OK ? st : bfail(b, DGX_EHIP, std::string("hipStreamEndCapture: ") + hipGetErrorString(e));
   }
-  if (e != hipSuccess) return bfail(b, DGX_EHIP, std::string("hipStreamEndCapture: ") + hipGetErrorString(e));
-  b->graph = g;
-  BHIP(b, hipGraphInstantiate(&b->gexec, g, nullptr, nullptr, 0));
-  b->graph_cfl = cfl;
+  g.graph = graph;
+  BHIP(b, hipGraphInstantiate(&g.exec, graph, nullptr, nullptr, 0));
+  g.cfl = cfl;
   return DGX_OK;
+}
+
+// The last step of an odd count.  Replayed from a graph, whose branches overlap the groups (five runs
+// of 8^3 to 24^3, two in lines: a call of one step 1 322 us, 1 421 with the groups in turn, 1 526 with
+// every run in k_batch_stage).  In turn where that is not worth a recording or not possible: one
+// group, the first such call with a cfl, a stream that the caller is recording.  (Branches beside the
+// caller's stream without a graph are no faster than in turn when their streams share a hardware
+// queue with it.)
+dgx_status odd_step(dgx_batch b, double cfl) {
+  const bool again = b->odd_cfl == cfl;
+  b->odd_cfl = cfl;
+  hipStreamCaptureStatus rec = hipStreamCaptureStatusNone;
+  if (b->groups.size() > 1 && again) BHIP(b, hipStreamIsCapturing(b->stream, &rec));
+  if (b->groups.size() < 2 || !again || rec != hipStreamCaptureStatusNone)
+    return enqueue_step(b, b->stream, cfl, 0, false, false);
+  dgx_status st = ensure_graph(b, 1, cfl);
+  if (st == DGX_OK) BHIP(b, hipGraphLaunch(b->steps[0].exec, b->stream));
+  return st;
 }
 
 }  // namespace
@@ -341,6 +364,19 @@ dgx_status dgx_batch_create(const dgx_config* cfgs, int32_t nruns, void* hip_str
   bool up = upload_desc(b) == DGX_OK && set_shape(b, 256, 0) == DGX_OK;
   for (int gi = dgx_batch_s::PENCIL; up && gi < dgx_batch_s::GROUPS; ++gi)
     up = upload_group(b, gi, [](int N) { return batch_pencil_elems(N); }) == DGX_OK;
+  // The groups in the order of their branches.  A graph's branches are submitted one after the other,
+  // so where one group holds nearly all the work (pair fluxes) it comes first: two steps of N = 3 28^3
+  // with 8^3 558 us, 580 in the other order; N = 4 24^3 with 3 8^3 787 / 818.  Else the tiles do (seven
+  // runs 2 313 us, 2 355 with the most work first; five runs 2 385 / 2 425).
+  double work[dgx_batch_s::GROUPS] = {}, total = 0.0;
+  for (int gi = dgx_batch_s::TILED; gi < dgx_batch_s::GROUPS; ++gi) {
+    for (int r : b->order[gi]) work[gi] += (double)b->nodes[r] * b->desc[r].N;
+    if (!b->order[gi].empty()) b->groups.push_back(gi);
+    total += work[gi];
+  }
+  const auto most = std::max_element(b->groups.begin(), b->groups.end(),
+                                     [&](int x, int y) { return work[x] < work[y]; });
+  if (total < 1.1 * work[*most]) std::rotate(b->groups.begin(), most, most + 1);
   if (!up) {
     dgx_batch_destroy(b);
     return DGX_EHIP;
@@ -380,12 +416,12 @@ dgx_status dgx_batch_step(dgx_batch b, double* const* u, int32_t nsteps, double 
   BHIP(b, batch_maxspeed(b->stream, all, b->budget, round8(all.total)));
   int pairs = nsteps / 2;
   if (pairs > 0) {
-    st = ensure_graph(b, cfl);
+    st = ensure_graph(b, 2, cfl);
     if (st != DGX_OK) return st;
-    for (int p = 0; p < pairs; ++p) BHIP(b, hipGraphLaunch(b->gexec, b->stream));
+    for (int p = 0; p < pairs; ++p) BHIP(b, hipGraphLaunch(b->steps[1].exec, b->stream));
   }
   if (nsteps % 2) {
-    st = enqueue_step(b, b->stream, cfl, 0, false, false);
+    st = odd_step(b, cfl);
     if (st != DGX_OK) return st;
     int64_t mx = 0;
     for (int64_t v : b->nodes) mx = std::max(mx, 5 * v);
@@ -404,7 +440,11 @@ dgx_status dgx_batch_rhs(dgx_batch b, const double* const* u, double* const* du)
   }
   dgx_status st = bind(b, const_cast<double* const*>(u), du, nullptr);
   if (st != DGX_OK) return st;
-  return enqueue_stage(b, b->stream, EPI_RHS, 0, 0.0, 0.0, 0, 0);
+  // in turn: a right-hand side is too short for the waits of a fork and join (28^3 and 8^3, N = 3:
+  // 46 us, 54 on branches)
+  return branch_groups(b, b->stream, false, [&](int gi, hipStream_t sg) {
+    return enqueue_group(b, sg, gi, EPI_RHS, 0, 0.0, 0.0, 0, 0);
+  });
 }
 
 dgx_status dgx_batch_tune(dgx_batch b, double* const* u, int32_t budget_ms) {
@@ -431,7 +471,8 @@ dgx_status dgx_batch_tune(dgx_batch b, double* const* u, int32_t budget_ms) {
       bool fail = false;
       for (int rep = 0; rep < 4 && !fail; ++rep) {
         fail |= hipEventRecord(e0, b->stream) != hipSuccess;
-        fail |= enqueue_stage(b, b->stream, EPI_RHS, 0, 0.0, 0.0, 0, 0) != DGX_OK;
+        for (int gi : b->groups)
+          fail |= enqueue_group(b, b->stream, gi, EPI_RHS, 0, 0.0, 0.0, 0, 0) != DGX_OK;
         fail |= hipEventRecord(e1, b->stream) != hipSuccess;
         fail |= hipEventSynchronize(e1) != hipSuccess;
         fail |= hipEventElapsedTime(&ms, e0, e1) != hipSuccess;
