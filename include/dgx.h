@@ -267,10 +267,11 @@ dgx_status dgx_batch_step(dgx_batch b, double *const *u, int32_t nsteps, double 
                           double *t);
 /* du_r = R_r(u_r) for every run (host arrays of device pointers). */
 dgx_status dgx_batch_rhs(dgx_batch b, const double *const *u, double *const *du);
-/* Autotuner: time one right-hand side of every run (written into the library's RK
- * registers; the states u are only read) for each candidate tile shape (threads per block:
+/* Autotuner: time one right-hand side of the runs in element tiles (written into the library's
+ * RK registers; the states u are only read) for each candidate tile shape (threads per block:
  * 256 or 512, i.e. elements per work item) and persistent grid (2, 4 or 8 blocks per CU,
- * or one block per work item) and keep the fastest.  budget_ms bounds the tuning time. */
+ * or one block per work item) and keep the fastest; without such runs the shape stays as it
+ * is.  budget_ms bounds the tuning time. */
 dgx_status dgx_batch_tune(dgx_batch b, double *const *u, int32_t budget_ms);
 /* Set the tile shape by hand: block = 256 or 512 threads; grid = 0 for one block per work
  * item, or a positive multiple of 8 (8 XCDs): a grid smaller than the number of work items

@@ -449,12 +449,18 @@ dgx_status dgx_batch_rhs(dgx_batch b, const double* const* u, double* const* du)
 
 dgx_status dgx_batch_tune(dgx_batch b, double* const* u, int32_t budget_ms) {
   if (!b || !u) return DGX_EINVAL;
-  // times one right-hand side of every run (written into the RK registers, which hold no
-  // state between steps) for each candidate tile shape and persistent grid
+  // times one right-hand side of the runs in element tiles (written into the RK registers, which
+  // hold no state between steps) for each candidate tile shape and persistent grid; the runs with
+  // a line of nodes per thread do not depend on them
   std::vector<double*> kbuf(b->nruns);
   for (int r = 0; r < b->nruns; ++r) kbuf[r] = b->desc[r].k;
   dgx_status st = bind(b, u, kbuf.data(), nullptr);
   if (st != DGX_OK) return st;
+  auto unbind = [&]() {
+    for (int r = 0; r < b->nruns; ++r) b->desc[r].du = nullptr;
+    return upload_desc(b);
+  };
+  if (b->order[dgx_batch_s::TILED].empty()) return unbind();
   hipEvent_t e0, e1;
   BHIP(b, hipEventCreate(&e0));
   BHIP(b, hipEventCreate(&e1));
@@ -471,8 +477,7 @@ dgx_status dgx_batch_tune(dgx_batch b, double* const* u, int32_t budget_ms) {
       bool fail = false;
       for (int rep = 0; rep < 4 && !fail; ++rep) {
         fail |= hipEventRecord(e0, b->stream) != hipSuccess;
-        for (int gi : b->groups)
-          fail |= enqueue_group(b, b->stream, gi, EPI_RHS, 0, 0.0, 0.0, 0, 0) != DGX_OK;
+        fail |= enqueue_group(b, b->stream, dgx_batch_s::TILED, EPI_RHS, 0, 0.0, 0.0, 0, 0) != DGX_OK;
         fail |= hipEventRecord(e1, b->stream) != hipSuccess;
         fail |= hipEventSynchronize(e1) != hipSuccess;
         fail |= hipEventElapsedTime(&ms, e0, e1) != hipSuccess;
@@ -493,8 +498,7 @@ dgx_status dgx_batch_tune(dgx_batch b, double* const* u, int32_t budget_ms) {
   }
   (void)hipEventDestroy(e0);
   (void)hipEventDestroy(e1);
-  for (int r = 0; r < b->nruns; ++r) b->desc[r].du = nullptr;
-  st = upload_desc(b);
+  st = unbind();
   if (st != DGX_OK) return st;
   return set_shape(b, bb, bg);
 }

@@ -74,3 +74,18 @@ def test_odd_steps_recorded_by_the_caller():
                 assert torch.equal(u, r), (rep, i)
             us[0].mul_(1.0)
         assert b.check() == 0
+
+
+def test_tuning_ranks_the_tiled_runs_only():
+    """The tile shape is that of the runs in element tiles: with none of them tuning leaves it alone
+    (timings of launches that do not depend on it would pick one by chance)."""
+    _, b, us = _batch([(5, 24), (4, 24), (3, 28)])
+    before = [u.clone() for u in us]
+    shape = b.set_shape(256, 0)
+    for _ in range(8):
+        assert b.tune(us, budget_ms=200) == shape
+    b.step(us, 2, cfl=0.3)
+    singles = [dgx.Solver(**inputs.ensemble_config(dict(N=N, K=K))) for N, K in [(5, 24), (4, 24), (3, 28)]]
+    for s, u0, u in zip(singles, before, us):
+        s.step(u0, 2, cfl=0.3)
+        assert torch.equal(u, u0)
