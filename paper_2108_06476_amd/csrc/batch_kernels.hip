@@ -74,7 +74,8 @@ __device__ __forceinline__ void batch_tile(unsigned char* smem, const double* sT
                                            int kw) {
   using L = typename StageLdsOf<3, N, VOL_EC, RT, BUDGET>::type;
   const StageArgs a = run_args(d, cur, A, B, emit, kw);
-  stage_tile<3, N, VOL_EC, EPI, RT, BUDGET>(*reinterpret_cast<L*>(smem), sT, a, run_geom(d), tile);
+  constexpr int STORE = sizeof(RT) == 4 ? STORE_ASK : STORE_PLAIN;
+  stage_tile<3, N, VOL_EC, EPI, RT, BUDGET, STORE>(*reinterpret_cast<L*>(smem), sT, a, run_geom(d), tile);
 }
 
 __device__ __forceinline__ void batch_item_tables(const RunDesc& d, double* sT, int budget) {

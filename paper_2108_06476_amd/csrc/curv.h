@@ -186,7 +186,7 @@ __device__ __forceinline__ void surface_dir_curv(const L& s, const Geom& g, int 
 
 // One tile of curvilinear elements (3D, float64).  The tables hold -S and +-1/w (the
 // reference element's own scale); the metric terms carry the geometry.
-template <int N, int VOL, int EPI>
+template <int N, int VOL, int EPI, int STORE = STORE_PLAIN>
 __device__ __forceinline__ void stage_tile_curv(typename CurvLdsOf<N, VOL>::type& s,
                                                 const double* sT, const StageArgs& a,
                                                 const Geom& g, int tile) {
@@ -282,7 +282,7 @@ __device__ __forceinline__ void stage_tile_curv(typename CurvLdsOf<N, VOL>::type
     }
   }
   // next-step wave speed per reference direction: (|v . Ja^d| + c |Ja^d|) / J
-  stage_epilogue<3, N, 5, EPI, 256>(
+  stage_epilogue<3, N, 5, EPI, 256, STORE>(
       s.xb, a, g, le, node, e, inb, active, ENN, own_ix, um, R,
       [&](const double (&un)[5], double (&ls)[3]) {
         Prim<double> q;
@@ -305,6 +305,15 @@ __global__ __launch_bounds__((Shape<3, N>::THREADS)) void k_stage_curv(StageArgs
   __shared__ double sT[TAB_SIZE];
   for (int i = threadIdx.x; i < TAB_SIZE; i += blockDim.x) sT[i] = g.tab[i];
   stage_tile_curv<N, VOL, EPI>(s, sT, a, g, (int)xcd_tile(blockIdx.x, gridDim.x));
+}
+
+// The RK stage of meshes past the cache (a.nt_out).
+template <int N, int VOL>
+__global__ __launch_bounds__((Shape<3, N>::THREADS)) void k_stage_curv_nt(StageArgs a, Geom g) {
+  __shared__ typename CurvLdsOf<N, VOL>::type s;
+  __shared__ double sT[TAB_SIZE];
+  for (int i = threadIdx.x; i < TAB_SIZE; i += blockDim.x) sT[i] = g.tab[i];
+  stage_tile_curv<N, VOL, EPI_RK, STORE_NT>(s, sT, a, g, (int)xcd_tile(blockIdx.x, gridDim.x));
 }
 
 // Small curvilinear meshes: a stage of a few elements is a chain of single-wave latencies (the
@@ -419,7 +428,7 @@ __global__ __launch_bounds__(256) void k_stage_curv_split(StageArgs a, Geom g) {
     R[v] = (((s.x[0][v][node] + s.x[1][v][node]) + s.x[2][v][node]) + s.x[3][v][node]) * ij +
            s.src[v][node];
   // wave 0 alone: the epilogue's element-wide reductions are wave reductions
-  stage_epilogue<3, N, 5, EPI, 256, false>(
+  stage_epilogue<3, N, 5, EPI, 256, STORE_PLAIN>(
       nullptr, a, g, 0, node, e, true, true, ENN, own_ix, um, R,
       [&](const double (&unew)[5], double (&ls)[3]) {
         Prim<double> q;

@@ -555,6 +555,11 @@ struct StageArgs {
 inline int stream_output(size_t state_bytes, size_t metric_bytes) {
   return 3 * state_bytes + metric_bytes > (metric_bytes ? (size_t)256 << 20 : (size_t)310000000);
 }
+// How a stage's epilogue stores uout: plainly, past the cache, or as a.nt_out says (STORE_ASK).
+// Where it can, the launch picks a kernel of the first two kinds (k_stage, k_stage_nt): the branch
+// of the third costs short stages up to 3 % (central 8^3 35.6 us per step, 36.8 with it).
+enum { STORE_PLAIN = 0, STORE_NT = 1, STORE_ASK = 2 };
+
 // store(v, nt) for v in [0, NV): one uniform branch.  (The empty asm on one side keeps the
 // compiler from merging the two sides' stores, which would drop the non-temporal hint.)
 template <int NV, typename Store>
@@ -703,10 +708,7 @@ __device__ __forceinline__ void weak_dir(const L& s, int base, int node, const d
 // xb: the block's per-element LDS slots (elements of several waves reduce through them).
 // DTF: the caller may ask for the first stage's dt to be derived here (a.dt_from) and for
 // the last stage's wave speeds to be folded into slots (a.speed_slots).
-// STREAM: uout may go past the cache (a.nt_out); off in kernels of meshes that fit it, whose short
-// stages the extra branch lengthens (5^3 warped mesh 0.7 %).
-template <int DIM, int N, int NV, int EPI, int BUDGET, bool STREAM = true, bool DTF = false,
-          typename SpeedFn>
+template <int DIM, int N, int NV, int EPI, int BUDGET, int STORE, bool DTF = false, typename SpeedFn>
 __device__ __forceinline__ double stage_epilogue(unsigned char* xb, const StageArgs& a,
                                                const Geom& g, int le, int node, int e, bool inb,
                                                bool active, size_t ENN, size_t own_ix,
@@ -749,10 +751,11 @@ __device__ __forceinline__ double stage_epilogue(unsigned char* xb, const StageA
         const size_t pb = (size_t)(own_ix - node) + (size_t)v * ENN;   // uniform plane base
         if (a.kw) a.k[pb + (unsigned)node] = kv[v];
         un[v] = um[v] + a.B * kv[v];
-        if constexpr (!STREAM) a.uout[pb + (unsigned)node] = un[v];
+        if constexpr (STORE == STORE_PLAIN) a.uout[pb + (unsigned)node] = un[v];
+        if constexpr (STORE == STORE_NT) __builtin_nontemporal_store(un[v], &a.uout[pb + (unsigned)node]);
         if (un_out) un_out[v] = un[v];
       }
-      if constexpr (STREAM)
+      if constexpr (STORE == STORE_ASK)
         store_out<NV>(a.nt_out, [&](int v, auto nt) {
           store_one(a.uout + (size_t)(own_ix - node) + (size_t)v * ENN + (unsigned)node, un[v], nt);
         });
@@ -935,7 +938,7 @@ __device__ __forceinline__ void indicator_elem(double* w0, double* w1, double* w
 
 // One tile of elements (the body of the stage kernels).  sT holds the run's operator
 // tables in LDS; they are loaded by the caller and become visible at the first barrier.
-template <int DIM, int N, int VOL, int EPI, typename RT, int BUDGET>
+template <int DIM, int N, int VOL, int EPI, typename RT, int BUDGET, int STORE = STORE_PLAIN>
 __device__ __forceinline__ void stage_tile(typename StageLdsOf<DIM, N, VOL, RT, BUDGET>::type& s,
                                            const double* sT, const StageArgs& a, const Geom& g,
                                            int tile) {
@@ -1119,10 +1122,7 @@ __device__ __forceinline__ void stage_tile(typename StageLdsOf<DIM, N, VOL, RT, 
         for (int d = 0; d < DIM; ++d) ls[d] = sT[TAB_JAC + d] * (fabs(q.v[d]) + q.c);
         return ok;
       };
-  // The float64 flux-differencing kernels of N >= 3 serve the meshes below use_pencil's line,
-  // which fit the cache; the branch of the streaming store costs them 3 % (8^3 to 10^3).
-  constexpr bool STREAM = !(VOL == VOL_EC && sizeof(RT) == 8 && (DIM == 2 || N >= 3));
-  const double dt_used = stage_epilogue<DIM, N, NV, EPI, BUDGET, STREAM, true>(
+  const double dt_used = stage_epilogue<DIM, N, NV, EPI, BUDGET, STORE, true>(
       s.xb, a, g, le, node, e, inb, active, ENN, own_ix, um, R, speeds, IND ? un : nullptr);
   // shock capturing: the raw indicator of the state just written, for the next stage (the
   // computation of k_indicator on the same values, in the element's LDS slot)
@@ -1156,6 +1156,16 @@ void k_stage(StageArgs a, Geom g) {
   __shared__ double sT[TAB_SIZE];
   for (int i = threadIdx.x; i < TAB_SIZE; i += blockDim.x) sT[i] = g.tab[i];
   stage_tile<DIM, N, VOL, EPI, RT, 256>(s, sT, a, g, (int)xcd_tile(blockIdx.x, gridDim.x));
+}
+
+// The RK stage of meshes past the cache (a.nt_out).
+template <int DIM, int N, int VOL, typename RT>
+__global__ __launch_bounds__((Shape<DIM, N>::THREADS), (VOL == VOL_WEAK_MFMA ? 4 : 1))
+void k_stage_nt(StageArgs a, Geom g) {
+  __shared__ typename StageLdsOf<DIM, N, VOL, RT>::type s;
+  __shared__ double sT[TAB_SIZE];
+  for (int i = threadIdx.x; i < TAB_SIZE; i += blockDim.x) sT[i] = g.tab[i];
+  stage_tile<DIM, N, VOL, EPI_RK, RT, 256, STORE_NT>(s, sT, a, g, (int)xcd_tile(blockIdx.x, gridDim.x));
 }
 
 // --------------------------------------------------------------------------------------

@@ -185,7 +185,9 @@ __global__ __launch_bounds__((Shape<3, N>::THREADS)) void k_stage_mhd(StageArgs 
   mhd_dir<N, 0>(s, g, a, sT, active, e, ec, base, node, um, qm, R);
   mhd_dir<N, 1>(s, g, a, sT, active, e, ec, base, node, um, qm, R);
   mhd_dir<N, 2>(s, g, a, sT, active, e, ec, base, node, um, qm, R);
-  stage_epilogue<3, N, 8, EPI, 256, N != 3>(
+  // (N = 3 past the cache runs in lines; as kernels of their own the others were no faster: N = 7 6^3
+  // 75.4 us per step, 78.9 with a plain kernel, 75.5 before either)
+  stage_epilogue<3, N, 8, EPI, 256, N == 3 ? STORE_PLAIN : STORE_ASK>(
       s.xb, a, g, le, node, e, inb, active, ENN, own_ix, um, R,
       [&](const double (&un)[8], double (&ls)[3]) {
         MhdPrim q;
@@ -445,7 +447,8 @@ __global__ __launch_bounds__((Shape<3, N>::THREADS), 3) void k_stage_mhd_ec(Stag
 #pragma unroll
     for (int v = 0; v < 8; ++v) R[v] += x[v * NN + node];
   }
-  stage_epilogue<3, N, 8, EPI, 256, N != 3>(
+  // (stored plainly on any mesh: N = 4 26^3 1 040 us per step, 1 081 past the cache)
+  stage_epilogue<3, N, 8, EPI, 256, STORE_PLAIN>(
       s.xb, a, g, le, node, e, inb, active, ENN, own_ix, um, R,
       [&](const double (&un)[8], double (&ls)[3]) {
         MhdPrim q;
@@ -558,7 +561,7 @@ __global__ __launch_bounds__(192) void k_stage_mhd_split(StageArgs a, Geom g) {
 #pragma unroll
   for (int v = 0; v < 8; ++v) R[v] = (s.x[0][v][node] + s.x[1][v][node]) + s.x[2][v][node];
   // wave 0 alone: the epilogue's element-wide reductions are wave reductions
-  stage_epilogue<3, N, 8, EPI, 256, false>(
+  stage_epilogue<3, N, 8, EPI, 256, STORE_PLAIN>(
       nullptr, a, g, 0, node, e, true, true, ENN, own_ix, um, R,
       [&](const double (&un)[8], double (&ls)[3]) {
         MhdPrim q;

@@ -68,6 +68,15 @@ struct Launch {
 
   template <int VOL, int EPI, typename RT>
   static hipError_t stage1(hipStream_t st, const StageArgs& a, const Geom& g) {
+    // (float64 flux differencing with N >= 3 or in 2D stores plainly: 3D meshes past the cache run
+    // in lines, but for the EC or no surface flux and N = 7 below use_pencil's line)
+    constexpr bool NT = EPI == EPI_RK && !(VOL == VOL_EC && sizeof(RT) == 8 && (DIM == 2 || N >= 3));
+    if constexpr (NT) {
+      if (a.nt_out) {
+        hipLaunchKernelGGL((k_stage_nt<DIM, N, VOL, RT>), dim3(blocks(g.E)), dim3(S::THREADS), 0, st, a, g);
+        return hipGetLastError();
+      }
+    }
     hipLaunchKernelGGL((k_stage<DIM, N, VOL, EPI, RT>), dim3(blocks(g.E)), dim3(S::THREADS), 0, st,
                        a, g);
     return hipGetLastError();
@@ -176,6 +185,12 @@ struct Launch {
     if constexpr (N == 3) {
       if (g.E <= CURV_SPLIT_MAX_E) {   // small meshes: four waves per element
         hipLaunchKernelGGL((k_stage_curv_split<VOL, EPI>), dim3((unsigned)g.E), dim3(256), 0, st, a, g);
+        return hipGetLastError();
+      }
+    }
+    if constexpr (EPI == EPI_RK && N == 3) {   // (others gain nothing: N = 4 26^3 763 / 765 us per step)
+      if (a.nt_out) {
+        hipLaunchKernelGGL((k_stage_curv_nt<N, VOL>), dim3(blocks(g.E)), dim3(S::THREADS), 0, st, a, g);
         return hipGetLastError();
       }
     }
