@@ -401,6 +401,12 @@ static bool stage_derives_dt(dgx_handle h) {
 // and slot reads cost about as much, so those meshes keep k_dt_final.
 constexpr int64_t STAGE_SLOTS_MAX_E = 16384;
 
+// The line-per-thread stages that leave the slots or the stage's own dt out serve larger meshes.
+static_assert(PENCIL_MIN_E[0] >= STAGE_SLOTS_MAX_E && PENCIL_SHOCK_MIN_E >= STAGE_SLOTS_MAX_E, "N = 3");
+static_assert(mhd_pencil_min<3, VOL_WEAK, EPI_RK>() > STAGE_DT_MAX_E &&
+              mhd_pencil_min<3, VOL_EC, EPI_RK>() > STAGE_DT_MAX_E &&
+              mhd_pencil_min<5, VOL_WEAK, EPI_RK>() > STAGE_DT_MAX_E, "ideal MHD");
+
 static bool stage_slots(dgx_handle h) {
   return !h->curved && !h->mhd && h->E > STAGE_DT_MAX_E && h->E < STAGE_SLOTS_MAX_E;
 }

@@ -607,7 +607,7 @@ __device__ __forceinline__ void pencil_tile(PencilLds<N>& s, const StageArgs& a,
   using X = PencilPos<N>;
   constexpr int n = P::n, NL = P::NL, NN = P::NN;
   const PencilPlace<N> w(g, tile);
-  const int t = w.t, la = w.la, lb = w.lb, line = w.line, le = w.le, e = w.e;
+  const int la = w.la, lb = w.lb, line = w.line, le = w.le, e = w.e;
   const bool on = w.on;
   const size_t ENN = (size_t)g.E * NN;
   const ConstTab tab = const_tab(g.tab);
@@ -741,7 +741,7 @@ __device__ __forceinline__ void pencil_tile(PencilLds<N>& s, const StageArgs& a,
         for (int i = 0; i < n; ++i) st(a.du + v * ENN, ho, i, (v == 0 ? 0.5 : 0.25) * acc[i][v]);
     }
   } else {
-    const double dt = a.dt_from ? stage_dt_from_partials(a) : *a.dt;
+    const double dt = NL != 16 && a.dt_from ? stage_dt_from_partials(a) : *a.dt;
     const double dh = 0.5 * dt, dq = 0.25 * dt;
     // Variables whose loads are in flight at once.  N = 6 and 7: one; what the sums still hold leaves
     // no registers for more (N = 6 12^3 188 us per step, 193 with two, 204 with five; 24^3 1 250,
@@ -787,7 +787,7 @@ __device__ __forceinline__ void pencil_tile(PencilLds<N>& s, const StageArgs& a,
         });
     }
     phase_fence();
-    if (a.speed != nullptr || a.speed_slots != nullptr) {
+    if (a.speed != nullptr || (NL != 16 && a.speed_slots != nullptr)) {
       double l[3] = {0.0, 0.0, 0.0};
       bool ok = true;
 #pragma unroll
@@ -800,23 +800,19 @@ __device__ __forceinline__ void pencil_tile(PencilLds<N>& s, const StageArgs& a,
       }
       if (on && !ok) *g.flag = 1;
       const double lam = pencil_elem_speed<N>(&s.q[0][0], tab, w, l);
-      if (a.speed_slots) {
-        if constexpr (NL == 16) {   // one atomic per wave
-          const double mw = wave_max_lane63(on ? lam : 0.0);
-          if (t == 63) slot_max(a.speed_slots, tile, mw);
-        } else if (on && line == (NL == 64 ? 63 : 0)) {
-          slot_max(a.speed_slots, e, lam);
-        }
-      } else if (on && line == (NL == 64 ? 63 : 0)) {
-        a.speed[e] = lam;
+      if (on && line == (NL == 64 ? 63 : 0)) {   // (N = 3 meshes are all beyond the slots)
+        if (NL != 16 && a.speed_slots) slot_max(a.speed_slots, e, lam);
+        else a.speed[e] = lam;
       }
     }
     if constexpr (SC) {
       if (a.alpha_next) pencil_indicator<N>(&s.q[0][0], a, g, w, tab + TAB_VINV, um);
     }
-    if (a.t_step && blockIdx.x == 0 && threadIdx.x == 0) stage_time_publish(a, dt);
-    if (a.slots_clear && blockIdx.x == 0 && threadIdx.x < (unsigned)DT_SLOTS)
-      a.slots_clear[threadIdx.x * DT_SLOT_STRIDE] = 0.0;
+    if constexpr (NL != 16) {
+      if (a.t_step && blockIdx.x == 0 && threadIdx.x == 0) stage_time_publish(a, dt);
+      if (a.slots_clear && blockIdx.x == 0 && threadIdx.x < (unsigned)DT_SLOTS)
+        a.slots_clear[threadIdx.x * DT_SLOT_STRIDE] = 0.0;
+    }
   }
 }
 
@@ -837,11 +833,11 @@ __device__ __forceinline__ void pencil_tile(PencilLds<N>& s, const StageArgs& a,
 //          1 312 / 1 285 | 1 478 / 1 560,  23^3 1 594 / 1 467 | 1 684 / 1 636 | 1 924 / 1 918
 // The upper limit keeps the meshes beyond 2^28 nodes in k_stage, so that a state of 2^31 values can
 // be compared bit for bit with a small mesh's (one kernel for both; offsets here would reach 2^29).
+constexpr int64_t PENCIL_MIN_E[5] = {20480, 13500, 5400, 1331, 9261};   // N = 3..7
 inline bool use_pencil(int N, int64_t E, int surf) {
-  constexpr int64_t min_E[5] = {20480, 13500, 5400, 1331, 9261};   // N = 3..7
   if (N < 3 || N > 7 || (surf != SURF_LLF && surf != SURF_HLL)) return false;
   const int64_t nn = (int64_t)(N + 1) * (N + 1) * (N + 1);
-  return E >= min_E[N - 3] && E * nn <= ((int64_t)1 << 28);
+  return E >= PENCIL_MIN_E[N - 3] && E * nn <= ((int64_t)1 << 28);
 }
 // The same with shock capturing (N = 3; single-wave blocks: 64^3 3 590 us per step, 3 630 with
 // two waves, 3 700 with four).  Sedov blast, microseconds per step: 16^3 109 / 122, 20^3 168 / 166,
@@ -850,8 +846,9 @@ inline bool use_pencil(int N, int64_t E, int surf) {
 // without blending the same in 65: what bounds it beyond memory are the waves of blending
 // elements, whose lines form three subcell fluxes more in each direction, and the indicator's
 // three passes through the LDS.
+constexpr int64_t PENCIL_SHOCK_MIN_E = 16384;
 inline bool use_pencil_shock(int64_t E, int surf) {
-  return E >= 16384 && E <= ((int64_t)1 << 22) && (surf == SURF_LLF || surf == SURF_HLL);
+  return E >= PENCIL_SHOCK_MIN_E && E <= ((int64_t)1 << 22) && (surf == SURF_LLF || surf == SURF_HLL);
 }
 // Four waves per block (x neighbours share an L1: N = 3, 64^3 3 040 us per step, against 3 240
 // with one) from here on; below, single-wave blocks even out the last round (32^3: 342 / 358).

@@ -475,7 +475,7 @@ __device__ __forceinline__ void mhd_pencil_tile(MhdPencilLds<N>& s, const StageA
           st(a.du + v * ENN, ho, i, (v == 0 ? sc[0] : v == 4 ? sc[2] : sc[1]) * acc[i][v]);
     }
   } else {
-    const double dt = a.dt_from ? stage_dt_from_partials(a) : *a.dt;
+    const double dt = *a.dt;   // (these meshes are beyond those whose stages derive it)
     // two variables at a time: all loads in flight at once would take 128 registers
 #pragma unroll
     for (int v0 = 0; v0 < 8; v0 += 2) {
@@ -528,7 +528,6 @@ __device__ __forceinline__ void mhd_pencil_tile(MhdPencilLds<N>& s, const StageA
       const double lam = pencil_elem_speed<N>(&s.q[0][0], tab, w, l);
       if (w.on && w.line == (NL == 64 ? 63 : 0)) a.speed[w.e] = lam;
     }
-    if (a.t_step && blockIdx.x == 0 && threadIdx.x == 0) stage_time_publish(a, dt);
   }
 }
 
