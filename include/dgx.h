@@ -237,7 +237,7 @@ dgx_status dgx_create_mhd(const dgx_mhd_config *cfg, void *hip_stream, dgx_handl
  * stages, and for dgx_rhs), so the time includes the launch gaps inside a run. */
 dgx_status dgx_profile_enable(dgx_handle h, int32_t on);
 /* Average duration in milliseconds of the timed kernel's launches since enable, and
- * its name (host string). */
+ * the name of the kernel of an RK stage (host string). */
 dgx_status dgx_profile_read(dgx_handle h, double *avg_ms, int64_t *launches, const char **name);
 
 /* ----- ensembles: many independent solvers advanced together ----- */
@@ -250,9 +250,11 @@ typedef struct dgx_batch_s *dgx_batch;
  * polydeg over the runs large enough for a line of nodes per thread.  The former takes one
  * block per work item unless the tuner (or dgx_batch_set_shape) picks a persistent grid
  * whose blocks loop over the items; one block per item is the default and what the tuner
- * normally keeps, since the persistent loop holds more registers live.  A step (per-run
- * dt + 5 stages) is replayed from a captured hipGraph, a branch for each of these launches'
- * runs.  The library owns each run's second
+ * normally keeps, since the persistent loop holds more registers live.  Steps (per-run
+ * dt + 5 stages) are replayed in pairs from a captured hipGraph, a branch for each of these
+ * launches' runs; the last of an odd count has a graph of its own, recorded when such a count
+ * comes a second time with the same cfl (the first time, with a single launch per stage and
+ * under a caller's capture its launches are issued in turn).  The library owns each run's second
  * state buffer and RK register (they are not passed in: a stage reads its input buffer's
  * face neighbours while it writes the other). */
 dgx_status dgx_batch_create(const dgx_config *cfgs, int32_t nruns, void *hip_stream,

@@ -951,7 +951,8 @@ dgx_status dgx_profile_read(dgx_handle h, double* avg_ms, int64_t* launches, con
   h->ev_count.clear();
   if (avg_ms) *avg_ms = h->launches ? h->prof_ms / h->launches : 0.0;
   if (launches) *launches = h->launches;
-  if (name) *name = h->L->volume_name;
+  if (name)
+    *name = h->L->stage_name(h->g, h->cfg.volume, h->cfg.surface, h->cfg.precision, h->curved, h->mhd);
   return DGX_OK;
 }
 

@@ -9,10 +9,10 @@
 //   - a line has one minus and one plus face, so the interface fluxes run with all lanes
 //     (k_stage: 2/n of them in each direction);
 //   - elements of several waves meet at five block barriers instead of one per pair round.
-// At N = 3 and 32^3 elements the right-hand side issues 1 738 vector instructions per four
+// At N = 3 and 32^3 elements the right-hand side issues 1 834 vector instructions per four
 // elements against 3 028 in k_stage.  What bounds it then is memory: at 64^3 elements a
-// Runge-Kutta stage moves 3.1 GB (counted between the L2s and the rest, 2.4 GB algorithmic) in
-// 600 us, 5.2 TB/s of the 6.0 TB/s that a copy reaches.
+// Runge-Kutta stage moves 2.9 GB (counted between the L2s and the rest, 2.4 GB algorithmic) in
+// 584 us, 4.9 TB/s of the 6.0 TB/s that a copy reaches (k_stage: 702 us).
 //
 // The lines change threads through LDS (five planes of the block's nodes): first the states
 // of the home lines (x), read in z and y layout; when the y lines are in registers the buffer
@@ -839,13 +839,13 @@ inline bool use_pencil(int N, int64_t E, int surf) {
   const int64_t nn = (int64_t)(N + 1) * (N + 1) * (N + 1);
   return E >= PENCIL_MIN_E[N - 3] && E * nn <= ((int64_t)1 << 28);
 }
-// The same with shock capturing (N = 3; single-wave blocks: 64^3 3 590 us per step, 3 630 with
-// two waves, 3 700 with four).  Sedov blast, microseconds per step: 16^3 109 / 122, 20^3 168 / 166,
-// 24^3 282 / 284, 27^3 398 / 358, 32^3 608 / 520, 48^3 1 717 / 1 550, 64^3 4 045 / 3 590; right-hand
-// side 24^3 54.5 / 54.3, 64^3 664 / 616.  A stage at 32^3 moves 336 MB in 93 us (3.6 TB/s), N = 3
-// without blending the same in 65: what bounds it beyond memory are the waves of blending
-// elements, whose lines form three subcell fluxes more in each direction, and the indicator's
-// three passes through the LDS.
+// The same with shock capturing (N = 3; single-wave blocks: two and four waves took 1 and 3 % more
+// at 64^3).  Sedov blast, microseconds per adaptive step, k_stage / k_pencil: 26 x 26 x 25 272 / 264,
+// 27^3 303 / 264, 32^3 454 / 377, 48^3 1 702 / 1 350, 64^3 3 986 / 3 190; right-hand side 27^3 58.7 /
+// 56.1, 64^3 661 / 544.  A stage at 32^3 moves 349 MB in 74 us (4.7 TB/s), N = 3 without blending
+// the same in 65: what bounds it beyond memory are the waves of blending elements, whose lines form
+// three subcell fluxes more in each direction, and the indicator's three passes through the LDS
+// (3 250 vector instructions per wave against 1 920).
 constexpr int64_t PENCIL_SHOCK_MIN_E = 16384;
 inline bool use_pencil_shock(int64_t E, int surf) {
   return E >= PENCIL_SHOCK_MIN_E && E <= ((int64_t)1 << 22) && (surf == SURF_LLF || surf == SURF_HLL);

@@ -552,9 +552,11 @@ constexpr int64_t mhd_pencil_min() {
   return -1;   // no such kernel
 }
 
-// What bounds it: memory.  A stage of the weak form at 32^3 moves 537 MB and takes 127 us, 4.2 TB/s
-// (139 with a node per thread); the volume and face work of the waves that wait (two per SIMD:
-// up to 249 registers, no spill) hides behind it.  One wave (N = 3) or element per block: blocks
+// What bounds it: memory.  A stage of the weak form at 32^3 moves 676 MB (counted between the L2s
+// and the rest, 544 MB algorithmic) in 125 us, 5.4 TB/s (143 us with a node per thread); the volume
+// and face work of the waves that wait hides behind it: two per SIMD at N = 3 (up to 252 registers)
+// and N = 4; at N = 5 (256 registers, up to four spilled) the LDS holds three blocks of two waves,
+// one and a half per SIMD.  One wave (N = 3) or element per block: blocks
 // of four waves, as k_pencil takes them on large meshes, measured 644 against 635 us at 32^3 and
 // 130 against 123 at 18^3.
 template <int N, int VOL, int EPI>

@@ -49,7 +49,8 @@ struct Launchers {
   // ideal MHD, weak form (3D only)
   hipError_t (*stage_mhd)(hipStream_t, const StageArgs&, const Geom&, int vol, int epi) = nullptr;
   hipError_t (*maxspeed_mhd)(hipStream_t, const double* u, double* partial, const Geom&) = nullptr;
-  const char* volume_name = "";
+  // the kernel of an RK stage (k_stage_nt and k_stage_curv_nt under their plain names)
+  const char* (*stage_name)(const Geom&, int vol, int surf, int prec, bool curved, bool mhd) = nullptr;
 };
 
 // Filled by the per-dimension translation units; nullptr if (dim, N) is not compiled.
@@ -272,6 +273,22 @@ struct Launch {
     return hipErrorInvalidValue;
   }
 
+  static const char* stage_name(const Geom& g, int vol, int surf, int prec, bool curved, bool mhd) {
+    if constexpr (DIM == 3) {
+      if (mhd) {
+        if (N == 3 && g.E <= MHD_SPLIT_MAX_E) return "k_stage_mhd_split";
+        constexpr int64_t weak = mhd_pencil_min<N, VOL_WEAK, EPI_RK>(), ec = mhd_pencil_min<N, VOL_EC, EPI_RK>();
+        const int64_t min_e = vol == VOL_EC ? ec : weak;
+        if (min_e >= 0 && g.E >= min_e && surf != SURF_NONE) return "k_pencil_mhd";
+        return vol == VOL_EC ? "k_stage_mhd_ec" : "k_stage_mhd";
+      }
+      if (curved) return N == 3 && g.E <= CURV_SPLIT_MAX_E ? "k_stage_curv_split" : "k_stage_curv";
+      if (vol == VOL_EC && prec == PREC_FP64 && use_pencil(N, g.E, surf)) return "k_pencil";
+      if (vol == VOL_SHOCKCAP && N == 3 && use_pencil_shock(g.E, surf)) return "k_pencil";
+    }
+    return "k_stage";
+  }
+
   static Launchers make() {
     Launchers L;
     L.threads = S::THREADS;
@@ -289,7 +306,7 @@ struct Launch {
       L.stage_mhd = &stage_mhd;
       L.maxspeed_mhd = &maxspeed_mhd;
     }
-    L.volume_name = "k_stage";
+    L.stage_name = &stage_name;
     return L;
   }
 };
