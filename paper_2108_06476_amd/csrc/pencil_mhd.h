@@ -535,7 +535,7 @@ __device__ __forceinline__ void mhd_pencil_tile(MhdPencilLds<N>& s, const StageA
 //   N = 3 weak  step  14^3 79 / 86, 16^3 105 / 105, 18^3 135 / 123, 20^3 169 / 149, 24^3 267 / 248,
 //                     28^3 436 / 409, 32^3 695 / 635, 40^3 1 375 / 1 216
 //               rhs   14^3 11.8 / 11.9, 16^3 15.7 / 13.7, 20^3 27.4 / 21.3, 32^3 96 / 80
-//   N = 3 EC    step  14^3 96 / 104, 16^3 126 / 127, 18^3 160 / 150, 24^3 316 / 312, 32^3 775 / 715,
+//   N = 3 EC    step  14^3 96 / 104, 16^3 126 / 127, 18^3 160 / 150, 24^3 321 / 317, 32^3 835 / 708,
 //                     40^3 1 533 / 1 435
 //               rhs   14^3 15.3 / 14.5, 16^3 20.3 / 17.2, 20^3 36.2 / 26.0, 32^3 129 / 93
 //   N = 4 weak  step  14^3 152 / 159, 20^3 338 / 378, 24^3 645 / 656, 32^3 1 535 / 1 626 (the
